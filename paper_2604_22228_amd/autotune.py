@@ -57,10 +57,10 @@ BATCH = (64,)
 # or 2 up to 8 ranks, 2 or 1 above; the 8-bit kernels load one row per lane
 # at a time)
 UNROLL = (2, 4)
-# 8-bit payloads: the kernels are bound by instruction issue and hide
-# memory latency with more resident waves and longer tiles
+# 8-bit payloads: a row holds four times the elements of a binary32 one, and
+# the row's arithmetic hides behind the loads of other waves
 TILES_8BIT = (16384, 32768, 65536)
-GROUPS_PER_CU_8BIT = (2, 3)
+GROUPS_PER_CU_8BIT = (1, 2, 3)
 # consecutive rows per tile too: the rows that share a line of block
 # scales are then read by one workgroup
 INTERLEAVE_8BIT = (0, 1, 4, 8, 16)

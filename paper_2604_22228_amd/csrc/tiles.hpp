@@ -446,19 +446,154 @@ struct VecTile {
 // number), codes enc(fl(y * fl(1/s))).
 // Tiles start on block boundaries (tile and partition lengths are multiples
 // of 256); only a bucket's last block can be short.
+// One word's four values times the block scale (one multiply each).
 template <class Fmt>
-__device__ __forceinline__ void dec16(const uint4& raw, float scale,
-                                      float (&o)[16]) {
-  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+__device__ __forceinline__ void dec4(uint32_t w, float scale, float (&o)[4]) {
+  auto lo = Fmt::template dec_pair<false>(w);
+  auto hi = Fmt::template dec_pair<true>(w);
+  o[0] = lo[0] * scale;
+  o[1] = lo[1] * scale;
+  o[2] = hi[0] * scale;
+  o[3] = hi[1] * scale;
+}
+
+// Rank-order sum of word k of every rank's codes, plain or Sum2.  dec(word,
+// rank, values) decodes one rank's word.  AGAIN: the rarely taken branch of
+// a caller that has decoded the same words already; the empty asm keeps the
+// compiler from holding those values in registers for it.
+template <bool COMP, bool AGAIN, int P, class Dec>
+__device__ __forceinline__ void sum_word(const uint4 (&raw)[P], int k,
+                                         Dec&& dec, float (&y)[4]) {
+  FSum<COMP, true> acc[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    auto lo = Fmt::template dec_pair<false>(w[k]);
-    auto hi = Fmt::template dec_pair<true>(w[k]);
-    o[4 * k + 0] = lo[0] * scale;
-    o[4 * k + 1] = lo[1] * scale;
-    o[4 * k + 2] = hi[0] * scale;
-    o[4 * k + 3] = hi[1] * scale;
+  for (int r = 0; r < P; ++r) {
+    float d[4];
+    uint32_t w = Word32::get(raw[r], k);
+    if (AGAIN) asm("" : "+v"(w));
+    dec(w, r, d);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (r == 0)
+        acc[j].init(d[j]);
+      else
+        acc[j].add(d[j]);
+    }
   }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) y[j] = acc[j].get();
+}
+
+// Whether the compensated sums of the 8-bit payloads go through binary64
+// (below): from 3 ranks on (64 buckets of e4m3, 2^29 values: 3 ranks 342 ->
+// 314 us, 4 ranks 423 -> 383 us, 16 ranks 1569 -> 1393 us).  At 1 and 2 ranks
+// Sum2 has no addition, or one, to compensate and costs less than the route.
+template <bool COMP, int P>
+constexpr bool kSumF64 = COMP && P >= 3;
+
+// What the binary64 route needs to know of a lane's terms.
+struct TermBound {
+  float t;   // a sum whose nonzero terms are all larger than t in magnitude
+             // is Sum2's exact case (see sum_word_f64)
+  double b;  // how far Sum2's s + c can be from the binary64 sum
+};
+
+// All terms of the lane are at most big = kMax max|s_r| in magnitude.  Where
+// a partial sum of P such terms could overflow, nothing is settled through
+// binary64 (t and b infinite).
+template <class Fmt, int P>
+__device__ __forceinline__ TermBound term_bound(const float (&s_in)[P]) {
+  // sum_{r=2}^{P-1} r (r + 3) / 2
+  constexpr int kC = ((P - 1) * P * (2 * P - 1) / 6 - 1 +
+                      3 * (P * (P - 1) / 2 - 1)) / 2;
+  float smax = fabsf(s_in[0]);
+#pragma unroll
+  for (int r = 1; r < P; ++r) smax = fmaxf(smax, fabsf(s_in[r]));
+  const bool far = !(smax < 0x1p126f / (Fmt::kMax * (float)P));
+  const float big = far ? __builtin_inff() : smax * Fmt::kMax;
+  return {big * ((float)(P * (P + 1) / 2) * 0x1p-24f),
+          (double)big * ((double)(kC + P) * 0x1p-48)};
+}
+
+// The Sum2 result of word k's four values, computed through binary64.
+//
+// Sum2 in binary32 costs seven dependent operations per rank and value,
+// which made these kernels wait for the VALU and not for memory.  A
+// binary64 running sum D costs two (convert, add), at the same rate, and
+// Sum2's result follows from it.  With u = 2^-24, E the exact sum and m the
+// bound on every |p_r|, Sum2 returns fl32(s + c) where s + sum e_r = E
+// exactly, |e_r| <= u (r + 1) m, and only c's own additions round:
+//   * every nonzero term larger than t = u m P (P + 1) / 2: the terms, so
+//     the e_r and c, are multiples of g >= u min|p_r|, and sum |e_r| < 2^24
+//     g: c is exact, so is D, and the result is D rounded;
+//   * else |s + c - E| <= u^2 m sum_{r=2}^{P-1} r (r + 3) / 2, and D is off
+//     by far less: with b the sum of both, D - b and D + b that round to the
+//     same binary32 value give the result, rounding being monotonic;
+//   * else Sum2 itself, for the word.
+// D's own ties are common (the terms have 24 bits each, so D often needs
+// just one more: 9 % of values), which is why the first test comes first: a
+// term below t appears in 0.2 % of gradient-like values, and one word in 20
+// then needs the third (which tells zero terms from small ones), one in 50
+// the last.  Sum2 never returns -0, which D rounds to only when every term
+// is -0: the second and third test give +0 there.
+//
+// Row of 1024 values at 8 ranks without its memory traffic, per SIMD: Sum2
+// 1776 ns, this about 980 ns.  The e4m3 kernel on 128 buckets, 2^30 values
+// in all, 8 ranks: 1.90 -> 1.65 ms (4.6 -> 5.3 TB/s), 5 % above the same
+// kernel with plain sums: what bounds it now is the memory streams.
+template <int P, class Dec>
+__device__ __forceinline__ void sum_word_f64(const uint4 (&raw)[P], int k,
+                                             Dec&& dec, const TermBound& tb,
+                                             float (&y)[4]) {
+  double D[4];
+  float least[4];
+#pragma unroll
+  for (int r = 0; r < P; ++r) {
+    float d[4];
+    dec(Word32::get(raw[r], k), r, d);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      D[j] = r == 0 ? (double)d[j] : D[j] + (double)d[j];
+      least[j] = r == 0 ? fabsf(d[j]) : fminf(least[j], fabsf(d[j]));
+    }
+  }
+  bool close = false;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    y[j] = (float)D[j];
+    close |= !(least[j] > tb.t);
+  }
+  if (__builtin_expect(__ballot(close) == 0, 1)) return;
+  bool open[4];
+  bool any = false;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float lo = (float)(D[j] - tb.b), hi = (float)(D[j] + tb.b);
+    open[j] = !(least[j] > tb.t) && !(lo == hi);
+    if (lo == hi) y[j] = hi;
+    any |= open[j];
+  }
+  if (__ballot(any) == 0) return;
+  // the smallest nonzero term: twice the magnitude's bits less one, which
+  // puts zero last
+  uint32_t nz[4] = {~0u, ~0u, ~0u, ~0u};
+#pragma unroll
+  for (int r = 0; r < P; ++r) {
+    float d[4];
+    uint32_t w = Word32::get(raw[r], k);
+    asm("" : "+v"(w));  // decoded again, not kept (see sum_word)
+    dec(w, r, d);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      nz[j] = min(nz[j], (__float_as_uint(d[j]) << 1) - 1u);
+  }
+  any = false;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const bool exact = nz[j] >= __float_as_uint(tb.t) << 1;
+    if (open[j] && exact) y[j] = (float)D[j] + 0.0f;
+    any |= open[j] && !exact;
+  }
+  if (__ballot(any) != 0) sum_word<true, true>(raw, k, dec, y);
 }
 
 __device__ __forceinline__ uint4 load_codes(const uint8_t* p, uint32_t have) {
@@ -496,26 +631,44 @@ struct Fp8Tile {
     // every rank's codes and scale are requested before the first is used,
     // so that one memory latency covers the row
     if (FULL) __builtin_amdgcn_sched_barrier(0);
-    FSum<COMP, true> acc[16];
-    {
-      float d[16];
-      dec16<Fmt>(raw[0], s_in[0], d);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc[j].init(d[j]);
-    }
-#pragma unroll
-    for (int r = 1; r < P; ++r) {
-      float d[16];
-      dec16<Fmt>(raw[r], s_in[r], d);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc[j].add(d[j]);
-    }
+    const auto dec = [&](uint32_t w, int r, float(&d)[4]) {
+      dec4<Fmt>(w, s_in[r], d);
+    };
     float y[16];
     float amax = 0.0f;
+    const auto keep = [&](int k, const float(&v)[4]) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      y[j] = acc[j].get();
-      if (FULL || (uint32_t)j < have) amax = fmaxf(amax, fabsf(y[j]));
+      for (int j = 0; j < 4; ++j) {
+        y[4 * k + j] = v[j];
+        if (FULL || (uint32_t)(4 * k + j) < have)
+          amax = fmaxf(amax, fabsf(v[j]));
+      }
+    };
+    if constexpr (kSumF64<COMP, P>) {
+      const TermBound tb = term_bound<Fmt>(s_in);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float v[4];
+        sum_word_f64(raw, k, dec, tb, v);
+        keep(k, v);
+      }
+      // infinite codes (e5m2): what Sum2 makes of them
+      if (__builtin_expect(__ballot(amax == __builtin_inff()) != 0, 0)) {
+        amax = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float v[4];
+          sum_word<true, true>(raw, k, dec, v);
+          keep(k, v);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float v[4];
+        sum_word<COMP, false>(raw, k, dec, v);
+        keep(k, v);
+      }
     }
     // max over the 16 lanes of the block
     amax = fmaxf(amax, __shfl_xor(amax, 8, 16));
@@ -602,21 +755,28 @@ __device__ __forceinline__ uint32_t mx_scale_byte(float amax) {
   return u < 0x00800000u ? 0u : (uint32_t)(max(e, -127) + 127);
 }
 
-// 16 codes (one lane's half block) scaled by the operand of byte b.
-__device__ __forceinline__ void mx_dec16(const uint4& raw, float scale,
-                                         float (&o)[16]) {
-  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const mx_f32x2 lo =
-        __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[k], scale, false);
-    const mx_f32x2 hi =
-        __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[k], scale, true);
-    o[4 * k + 0] = lo[0];
-    o[4 * k + 1] = lo[1];
-    o[4 * k + 2] = hi[0];
-    o[4 * k + 3] = hi[1];
-  }
+// A word's four codes scaled by the operand of byte b.
+__device__ __forceinline__ void mx_dec4(uint32_t w, float scale,
+                                        float (&o)[4]) {
+  const mx_f32x2 lo =
+      __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w, scale, false);
+  const mx_f32x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w, scale, true);
+  o[0] = lo[0];
+  o[1] = lo[1];
+  o[2] = hi[0];
+  o[3] = hi[1];
+}
+
+// Whether the exact sum, rounded once, is what Sum2 returns for a lane's
+// values (32 buckets, 2^28 values, 8 ranks: 0.606 -> 0.509 ms, 4.9 -> 5.9
+// TB/s, the time of plain sums; a row body 1540 -> 630 ns per SIMD): every decoded term is a multiple of g = 2^-9 2^(bmin - 127) of at
+// most 448 * 2^(bmax - 127), so for bmax - bmin <= 23 and up to 16 ranks
+// Sum2's errors add up to at most 135 u 448 2^(bmax - 127) <= 2^24 g: its
+// correction is exact and its result the exact sum rounded; and the
+// binary64 sum is exact too (22 + 23 bits).  Above byte 240 a partial sum
+// could leave binary32's range.
+__device__ __forceinline__ bool mx_exact(uint32_t bmin, uint32_t bmax) {
+  return bmax <= 240u && bmax - bmin <= 23u;
 }
 
 // Codes of y[0..16) / 2^(b - 127), four per word (code j in byte j).
@@ -677,27 +837,67 @@ struct MxTile {
       }
     }
     if (FULL) __builtin_amdgcn_sched_barrier(0);
-    FSum<COMP, true> acc[16];
-    {
-      float d[16];
-      mx_dec16(raw[0], e8m0_operand(b_in[0]), d);
+    const auto dec = [&](uint32_t w, int r, float(&d)[4]) {
+      mx_dec4(w, e8m0_operand(b_in[r]), d);
+    };
+    bool sum2 = COMP;  // the binary32 Sum2 itself
+    if constexpr (kSumF64<COMP, P>) {
+      uint32_t bmin = b_in[0], bmax = b_in[0];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc[j].init(d[j]);
-    }
+      for (int r = 1; r < P; ++r) {
+        bmin = min(bmin, b_in[r]);
+        bmax = max(bmax, b_in[r]);
+      }
+      bool exact = mx_exact(bmin, bmax);
+      if (__ballot(!exact) != 0) {
+        // all-zero blocks carry byte 0: their scale does not count
+        bmin = 255u;
+        bmax = 0u;
 #pragma unroll
-    for (int r = 1; r < P; ++r) {
-      float d[16];
-      mx_dec16(raw[r], e8m0_operand(b_in[r]), d);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc[j].add(d[j]);
+        for (int r = 0; r < P; ++r) {
+          const bool zero = ((raw[r].x | raw[r].y | raw[r].z | raw[r].w) &
+                             0x7f7f7f7fu) == 0u;
+          bmin = min(bmin, zero ? 255u : b_in[r]);
+          bmax = max(bmax, zero ? 0u : b_in[r]);
+        }
+        exact = bmin == 255u && bmax == 0u ? true : mx_exact(bmin, bmax);
+      }
+      sum2 = __ballot(!exact) != 0;
     }
     float y[16];
     float amax = 0.0f;
+    if (kSumF64<COMP, P> && !sum2) {
+      // binary64 running sums (exact here), rounded once; + 0 turns -0 into
+      // Sum2's +0
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      y[j] = acc[j].get();
-      if (FULL || (uint32_t)j < have) amax = fmaxf(amax, fabsf(y[j]));
+      for (int k = 0; k < 4; ++k) {
+        double D[4];
+#pragma unroll
+        for (int r = 0; r < P; ++r) {
+          float d[4];
+          dec(Word32::get(raw[r], k), r, d);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            D[j] = r == 0 ? (double)d[j] : D[j] + (double)d[j];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[4 * k + j] = (float)D[j] + 0.0f;
+        // one word at a time: the other words' terms would only hold
+        // registers
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float v[4];
+        sum_word<COMP, kSumF64<COMP, P>>(raw, k, dec, v);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[4 * k + j] = v[j];
+      }
     }
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (FULL || (uint32_t)j < have) amax = fmaxf(amax, fabsf(y[j]));
     amax = pair_max(amax);
     const uint32_t b = mx_scale_byte(amax);
     const uint4 codes = mx_enc16(y, e8m0_operand(b));
