@@ -272,12 +272,10 @@ int pcoll_pready_rank_on_stream(pcoll_req_t req, int rank,
 /* Non-blocking test of one partition (MPI_Parrived): *flag = 1 once its
  * output is final in the current (or last completed) epoch.  PCOLL_ERR_STATE before the first
  * start.  Arrival (Section 4.5: a partition counts only after all of its
- * chunks have landed) is signalled either by the partition's own flag,
- * which the kernel sets as soon as it has published the partition's last
- * tile, or by the retirement of the epoch's kernel with no error, which
- * implies every partition: the kernel leaves the tiles that a workgroup
- * still holds when the work runs out to its own end instead of publishing
- * them (config field publish_batch).  The second case costs one
+ * chunks have landed) is signalled by the partition's own flag, which the
+ * kernel sets once it has published the partition's last tile; the
+ * retirement of the epoch's kernel with no error implies every partition.
+ * For a partition whose flag is not set yet the call costs one
  * hipEventQuery. */
 int pcoll_parrived(pcoll_req_t req, int part, int *flag);
 
@@ -286,8 +284,8 @@ int pcoll_parrived(pcoll_req_t req, int part, int *flag);
  * Returns the epoch's error as pcoll_wait does. */
 int pcoll_test(pcoll_req_t req, int *flag);
 
-/* Blocks until every partition has arrived (by its flag, or by the
- * kernel's clean retirement; see pcoll_parrived) and the epoch is complete
+/* Blocks until every partition has arrived (see pcoll_parrived) and the
+ * epoch is complete
  * (Section 4.5, Final Synchronization: completion only after every chunk's
  * synchronization point; MPI_Wait of the MPI-4 model).
  * Returns PCOLL_ERR_ABORTED if the kernel gave up on its own deadline
@@ -355,12 +353,13 @@ typedef struct {
                         of the band starting at its row j */
   int group_waves;   /* wavefronts per workgroup (1..8); they share each
                         tile's rows */
-  int publish_batch; /* finished tiles a workgroup publishes with one
-                        release (1..64).  A workgroup also publishes before
-                        it waits for readied work, so the batch only delays
-                        arrival flags while the kernel has a backlog:
-                        larger amortizes the L2 writeback, smaller lets
-                        partitions arrive sooner under backlog */
+  int publish_batch; /* finished tiles a workgroup publishes at once
+                        (1..64).  A workgroup also publishes before it waits
+                        for readied work and when it runs out of work, so
+                        the batch only delays arrival flags while the kernel
+                        has a backlog: larger lets a workgroup's wavefronts
+                        run on without waiting for their stores, smaller
+                        lets partitions arrive sooner under backlog */
   int guide;         /* guided self-scheduling divisor f (0..64): a
                         partition queued with R rows of work left in the
                         epoch gets tiles of about R / (f x workgroups) rows,

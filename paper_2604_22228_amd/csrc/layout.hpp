@@ -29,16 +29,9 @@ struct BucketDesc {
   void* out;                        // reduced message
   void* out_scale;                  // 8-bit floats only: output scales
   uint64_t count;                   // elements in the bucket
-  uint64_t reserved;
-};
-
-// Per global partition, in device memory; read-only to the kernels.
-struct PartDesc {
-  uint64_t off;     // first element, relative to the bucket start
-  uint64_t len;     // elements (0 for empty partitions)
-  uint32_t bucket;  // owning bucket
-  uint32_t rows;    // ceil(len / row_elems): rows of 64 lanes x 16 bytes
-  uint64_t reserved;
+  uint64_t psize;                   // its partition length (the chunk rule):
+                                    // partition k is elements [k psize,
+                                    // (k + 1) psize) clipped to count
 };
 
 // One entry of the device work queue: partitions in the order they were
@@ -71,16 +64,25 @@ struct HostShared {
 struct EpochCounters {
   uint32_t claim;                 // tiles handed out beyond the first round
   uint32_t pad0[31];
-  uint64_t qstate;                // (queue entries << 32) | queued tiles
-  uint32_t pad1[30];
-  uint32_t ilock;                 // ingest lock (0 free, 1 held)
-  uint32_t hconsumed;             // host ready entries already queued
+  uint64_t qstate;                // kQLocked | kQDevice | (queue entries <<
+                                  // 32) | queued tiles
+  uint64_t consumed;              // with kQDevice: (device ring entries <<
+                                  // 32) | host ready entries consumed
   uint64_t queued_rows;           // rows of the partitions queued so far
-  uint32_t dconsumed;             // device ring entries already queued
-  uint32_t pad2[27];
+                                  // (guided tile sizes only)
+  uint32_t pad1[26];
   uint32_t error;                 // first error seen this epoch
   uint32_t pad3[31];
 };
+
+// The ingest lock is part of the queue state: one compare-and-swap takes it
+// and confirms that nothing was queued since the caller read the counts, and
+// one store publishes new counts and gives it up.  kQDevice: entries of the
+// device ready ring have been consumed this epoch.  Until then every queue
+// entry comes from the host list, which holds no duplicates, so the queue
+// entries are also the host entries consumed, and the word says it all.
+constexpr uint64_t kQLocked = 1ull << 63;
+constexpr uint64_t kQDevice = 1ull << 62;
 
 // Device ready rings.  Device-side signals of epoch e append to ring e & 1
 // (slots dlist[(e & 1) * nparts_total ...]).  Its reservation word holds
@@ -110,7 +112,6 @@ enum KernelStatus : uint32_t {
 // Kernel arguments (passed by value).
 struct ReduceArgs {
   const BucketDesc* buckets;
-  const PartDesc* parts;
   QEntry* queue;          // [nparts_total]
   uint32_t* done;         // [2][nparts_total] finished tiles per
                           // partition, one half per epoch parity
@@ -130,7 +131,9 @@ struct ReduceArgs {
   uint32_t nparts_total;
   uint32_t total_groups;   // workgroups of the launch
   uint64_t total_rows;     // rows of all partitions
-  uint32_t row_elems;      // elements per row (1024 bytes per rank)
+  uint32_t row_shift;      // log2 of the elements per row (1024 bytes per
+                           // rank)
+  uint32_t bucket_parts;   // partitions per bucket
   uint32_t min_tile_rows;  // bounds of the rows per tile chosen at queueing
   uint32_t max_tile_rows;
   uint32_t interleave;     // tile layout: 0 = consecutive rows, B > 0 =
@@ -140,6 +143,8 @@ struct ReduceArgs {
   uint32_t publish_batch;  // finished tiles a workgroup publishes together
   uint32_t epoch;          // stamp of this launch, or 0: read it from the
                            // host struct (a graph replays fixed arguments)
+  uint64_t count0, psize0; // the bucket's count and psize when there is one
+                           // bucket (bucket_parts = nparts_total)
   uint64_t timeout_ticks; // device wall-clock ticks before giving up
   uint64_t* trace;        // debug: per workgroup 4 words (wall-clock at
                           // entry, when its first tile was queued, after

@@ -1,8 +1,8 @@
 // The allocation-free form of one epoch: every buffer the reduce kernel
-// uses beyond its inputs and outputs (partition table, bucket descriptor,
-// work queue, counters, done counters, queued stamps, ready list) lives in
-// a file-scope device array of fixed size, so a call needs no hipMalloc
-// and no pinned host memory (for callers under graph capture or in loops
+// uses beyond its inputs and outputs (bucket descriptor, work queue,
+// counters, done counters, queued stamps, ready list) lives in a file-scope
+// device array of fixed size, so a call needs no hipMalloc and no pinned
+// host memory (for callers under graph capture or in loops
 // that must not allocate).  Each device holds its own copy of the array
 // until the process ends; calls on one device share it, so calls that
 // overlap on one device race.
@@ -40,8 +40,7 @@ hipError_t noalloc_scratch(int device, void** ptr) {
 }
 
 // Writes the state one epoch starts from into the scratch array: the
-// bucket descriptor, the partition table (the chunk rule: offsets k * psize,
-// lengths clipped to the message), cleared counters of both epoch parities,
+// bucket descriptor, cleared counters of both epoch parities,
 // cleared done counters and queued stamps, and a ready list that holds
 // every partition tagged with the epoch (all partitions ready at launch).
 // The device ready rings stay empty (reservation words 0).
@@ -62,15 +61,6 @@ __global__ __launch_bounds__(256) void noalloc_setup_kernel(NoallocSetup s) {
       (uint32_t)((2 * sizeof(EpochCounters) + 2 * sizeof(RingCounters)) / 4);
   if (i < nctr) reinterpret_cast<uint32_t*>(base + L.ctr)[i] = 0u;
   if (i < s.nparts) {
-    PartDesc p{};
-    const uint64_t off = (uint64_t)i * s.psize < s.count
-                             ? (uint64_t)i * s.psize
-                             : s.count;
-    p.off = off;
-    p.len = s.count - off < s.psize ? s.count - off : s.psize;
-    p.bucket = 0;
-    p.rows = (uint32_t)((p.len + s.row_elems - 1) / s.row_elems);
-    reinterpret_cast<PartDesc*>(base + L.parts)[i] = p;
     uint32_t* done = reinterpret_cast<uint32_t*>(base + L.done);
     done[i] = 0u;
     done[s.nparts + i] = 0u;

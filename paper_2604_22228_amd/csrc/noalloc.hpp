@@ -10,7 +10,7 @@
 namespace pcoll {
 
 // Size of the per-device scratch array, and the most partitions it holds
-// (80 bytes per partition plus about 2 KiB of fixed state).
+// (48 bytes per partition plus about 2 KiB of fixed state).
 constexpr size_t kNoallocScratchBytes = 512u * 1024u;
 constexpr uint32_t kNoallocMaxParts = 4096u;
 
@@ -18,7 +18,7 @@ constexpr uint32_t kNoallocMaxParts = 4096u;
 // hlist and arrived follow each other, as in the host-coherent block of a
 // request; the two ring words follow the two counter sets.
 struct NoallocLayout {
-  uint64_t parts, queue, done, queued, dlist, ctr, ring, bucket, host, hlist,
+  uint64_t queue, done, queued, dlist, ctr, ring, bucket, host, hlist,
       arrived, total;
 };
 
@@ -30,7 +30,6 @@ inline NoallocLayout noalloc_layout(uint32_t np) {
     off = (off + bytes + 255u) / 256u * 256u;
     return o;
   };
-  L.parts = take(sizeof(PartDesc) * np);
   L.queue = take(sizeof(QEntry) * np);
   L.done = take(sizeof(uint32_t) * 2 * np);
   L.queued = take(sizeof(uint32_t) * np);
@@ -50,10 +49,7 @@ struct NoallocSetup {
   unsigned char* base;  // the scratch array on this device
   NoallocLayout layout;
   BucketDesc bucket;
-  uint64_t count;       // elements of the message
-  uint64_t psize;       // partition length (the chunk rule)
   uint32_t nparts;
-  uint32_t row_elems;   // elements per row of 64 lanes x 16 bytes
   uint32_t epoch;
 };
 

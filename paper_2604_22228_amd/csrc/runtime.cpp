@@ -5,12 +5,11 @@
 // entry points of kernels.hpp.  Per request:
 //   * host-coherent pinned memory (HostShared + ready list + arrived flags)
 //     is the channel between the host thread and the running kernel:
-//     pready appends to the ready list and publishes its length with a
-//     store-release; the kernel stores arrived[p] = epoch when partition p
-//     is final, and an epoch-stamped status if it gives up; the host's wait
+//     pready appends epoch-tagged entries to the ready list; the kernel
+//     stores arrived[p] = epoch when partition p is final, and an epoch-stamped status if it gives up; the host's wait
 //     returns once every arrived flag carries the epoch;
-//   * device memory holds the partition table, the work queue and the
-//     counters the kernel's wavefronts share;
+//   * device memory holds the work queue and the counters the kernel's
+//     wavefronts share;
 //   * an LRU cache (Section 4.2's graph cache) maps each binding to its
 //     descriptor table and, in graph mode, to the instantiated graph of the
 //     persistent launch, created lazily on first start (Algorithm 1,
@@ -133,6 +132,15 @@ struct BindKeyHash {
   }
 };
 
+// One global partition (host side; the kernels compute theirs from the
+// bucket's count and partition length).
+struct PartDesc {
+  uint64_t off;     // first element, relative to the bucket start
+  uint64_t len;     // elements (0 for empty partitions)
+  uint32_t bucket;  // owning bucket
+  uint32_t rows;    // ceil(len / row_elems): rows of 64 lanes x 16 bytes
+};
+
 struct Binding {
   BucketDesc* table = nullptr;   // device copy of the bucket descriptors
   hipGraphExec_t exec = nullptr; // persistent launch, captured lazily
@@ -163,7 +171,6 @@ struct pcoll_req_s {
   uint32_t* arrived = nullptr;
 
   void* arena = nullptr;
-  PartDesc* d_parts = nullptr;
   QEntry* d_queue = nullptr;
   uint32_t* d_done = nullptr;     // [2][nparts_total]
   uint32_t* d_queued = nullptr;
@@ -557,7 +564,6 @@ int create(const std::vector<uint64_t>& counts, int dtype, int op,
     off = align_up(off + bytes, 256);
     return o;
   };
-  const size_t o_parts = take(sizeof(PartDesc) * np_total);
   const size_t o_queue = take(sizeof(QEntry) * np_total);
   const size_t o_done = take(sizeof(uint32_t) * 2 * np_total);
   const size_t o_queued = take(sizeof(uint32_t) * np_total);
@@ -573,15 +579,11 @@ int create(const std::vector<uint64_t>& counts, int dtype, int op,
                                                        : hip_fail(e, "hipMalloc");
   HIP_TRY(hipMemset(r->arena, 0, off));
   char* base = static_cast<char*>(r->arena);
-  r->d_parts = reinterpret_cast<PartDesc*>(base + o_parts);
   r->d_queue = reinterpret_cast<QEntry*>(base + o_queue);
   r->d_done = reinterpret_cast<uint32_t*>(base + o_done);
   r->d_queued = reinterpret_cast<uint32_t*>(base + o_queued);
   r->d_hits = reinterpret_cast<uint32_t*>(base + o_hits);
   r->d_tiles = reinterpret_cast<uint32_t*>(base + o_tiles);
-  HIP_TRY(hipMemcpy(r->d_parts, r->parts.data(),
-                    sizeof(PartDesc) * r->parts.size(),
-                    hipMemcpyHostToDevice));
   r->d_dlist = reinterpret_cast<uint64_t*>(base + o_dlist);
   r->d_dstamp = reinterpret_cast<uint32_t*>(base + o_dstamp);
   r->d_rank_marks = reinterpret_cast<uint64_t*>(base + o_marks);
@@ -613,7 +615,6 @@ int create(const std::vector<uint64_t>& counts, int dtype, int op,
 ReduceArgs make_args(const pcoll_req_s* r) {
   ReduceArgs a{};
   a.buckets = r->cur->table;
-  a.parts = r->d_parts;
   a.queue = r->d_queue;
   a.done = r->d_done;
   a.queued = r->d_queued;
@@ -628,7 +629,11 @@ ReduceArgs make_args(const pcoll_req_s* r) {
   a.nparts_total = r->nparts_total;
   a.total_groups = (uint32_t)r->groups;
   a.total_rows = r->total_rows;
-  a.row_elems = (uint32_t)row_elems(r->dtype);
+  a.row_shift = (uint32_t)__builtin_ctzll(row_elems(r->dtype));
+  a.bucket_parts = (uint32_t)r->nparts_per_bucket;
+  a.count0 = r->counts[0];
+  a.psize0 = plan_psize(r->counts[0], (uint64_t)r->nparts_per_bucket,
+                        part_align(r->dtype));
   a.min_tile_rows = (uint32_t)std::max<uint64_t>(
       1, (uint64_t)r->cfg.min_tile_elems / row_elems(r->dtype));
   a.max_tile_rows = (uint32_t)std::max<uint64_t>(
@@ -730,8 +735,7 @@ bool all_arrived(pcoll_req_s* r) {
 // Whether the epoch's launch has retired: 1 yes, 0 not yet, or a negative
 // error code (the HIP error is kept for pcoll_last_error_detail).  A launch
 // that retired with no error recorded has reduced every tile, and its end
-// made every store visible: then every partition has arrived, also those
-// whose last tiles the kernel left unpublished.
+// made every store visible: then every partition has arrived.
 int retired(pcoll_req_s* r) {
   const hipError_t q = hipEventQuery(r->ev_end);
   if (q == hipSuccess) return 1;
@@ -806,7 +810,10 @@ int spin_wait(pcoll_req_t r, int limit_ms) {
   auto t0 = std::chrono::steady_clock::now();
   bool aborted = false;
   for (uint64_t it = 0;; ++it) {
-    const int rc = poll_epoch(r, (it & 7) == 7);
+    // every partition's arrival and every error of the kernel show in the
+    // pinned block; the event, whose query costs a microsecond of runtime
+    // calls, only tells of a launch that failed
+    const int rc = poll_epoch(r, (it & 1023) == 1023);
     if (rc != 0) return rc < 0 ? rc : PCOLL_SUCCESS;
     _mm_pause();
     if (!aborted && limit_ms >= 0 && (it & 1023) == 1023 &&
@@ -938,6 +945,8 @@ int pcoll_bind(pcoll_req_t r, const void* const* rank_bufs, void* const* outs,
         d.out = outs[b];
         d.out_scale = out2 ? out_scales[b] : nullptr;
         d.count = r->counts[(size_t)b];
+        d.psize = plan_psize(d.count, (uint64_t)r->nparts_per_bucket,
+                             part_align(r->dtype));
       }
       Binding nb_{};
       HIP_TRY(hipMalloc(&nb_.table, sizeof(BucketDesc) * tab.size()));
@@ -1305,17 +1314,14 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
   s.bucket.out = out;
   s.bucket.out_scale = out2 ? out_scale : nullptr;
   s.bucket.count = count;
-  s.count = count;
-  s.psize = ps;
+  s.bucket.psize = ps;
   s.nparts = np;
-  s.row_elems = (uint32_t)re;
   s.epoch = 1;  // every stamp is rewritten by the set-up launch
   const hipStream_t st = static_cast<hipStream_t>(stream);
   HIP_TRY(launch_noalloc_setup(s, st));
 
   ReduceArgs a{};
   a.buckets = reinterpret_cast<const BucketDesc*>(base + L.bucket);
-  a.parts = reinterpret_cast<const PartDesc*>(base + L.parts);
   a.queue = reinterpret_cast<QEntry*>(base + L.queue);
   a.done = reinterpret_cast<uint32_t*>(base + L.done);
   a.queued = reinterpret_cast<uint32_t*>(base + L.queued);
@@ -1328,7 +1334,10 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
   a.nparts_total = np;
   a.total_groups = (uint32_t)groups;
   a.total_rows = total_rows;
-  a.row_elems = (uint32_t)re;
+  a.row_shift = (uint32_t)__builtin_ctzll(re);
+  a.bucket_parts = np;
+  a.count0 = count;
+  a.psize0 = ps;
   a.min_tile_rows =
       (uint32_t)std::max<uint64_t>(1, (uint64_t)c.min_tile_elems / re);
   a.max_tile_rows = (uint32_t)std::max<uint64_t>(1, (uint64_t)c.tile_elems / re);

@@ -259,36 +259,37 @@ template <class Acc, int P, int Kind>
 __device__ __forceinline__ void combine_scalar(const char* const (&in)[P],
                                                char* out, char* out2,
                                                uint32_t i) {
-  if (Kind == 3) {
+  if constexpr (Kind == 3) {
     Acc a;
     a.init(bf16_to_f(reinterpret_cast<const uint16_t*>(in[0])[i]));
 #pragma unroll
     for (int r = 1; r < P; ++r)
       a.add(bf16_to_f(reinterpret_cast<const uint16_t*>(in[r])[i]));
     uint32_t lo;
-    reinterpret_cast<uint16_t*>(out)[i] = (uint16_t)bf16_pair(a.get(), lo);
-    reinterpret_cast<uint16_t*>(out2)[i] = (uint16_t)lo;
-  } else if (Kind == 2) {
+    st_out(reinterpret_cast<uint16_t*>(out) + i,
+           (uint16_t)bf16_pair(a.get(), lo));
+    st_out(reinterpret_cast<uint16_t*>(out2) + i, (uint16_t)lo);
+  } else if constexpr (Kind == 2) {
     Acc a;
     a.init(bf16_to_f(reinterpret_cast<const uint16_t*>(in[0])[i]));
 #pragma unroll
     for (int r = 1; r < P; ++r)
       a.add(bf16_to_f(reinterpret_cast<const uint16_t*>(in[r])[i]));
-    reinterpret_cast<uint16_t*>(out)[i] = (uint16_t)f_to_bf16(a.get());
-  } else if (Kind == 0) {
+    st_out(reinterpret_cast<uint16_t*>(out) + i, (uint16_t)f_to_bf16(a.get()));
+  } else if constexpr (Kind == 0) {
     Acc a;
     a.init(as_f(reinterpret_cast<const uint32_t*>(in[0])[i]));
 #pragma unroll
     for (int r = 1; r < P; ++r)
       a.add(as_f(reinterpret_cast<const uint32_t*>(in[r])[i]));
-    reinterpret_cast<uint32_t*>(out)[i] = __float_as_uint(a.get());
+    st_out(reinterpret_cast<uint32_t*>(out) + i, __float_as_uint(a.get()));
   } else {
     Acc a;
     a.init(reinterpret_cast<const uint32_t*>(in[0])[i]);
 #pragma unroll
     for (int r = 1; r < P; ++r)
       a.add(reinterpret_cast<const uint32_t*>(in[r])[i]);
-    reinterpret_cast<uint32_t*>(out)[i] = a.get();
+    st_out(reinterpret_cast<uint32_t*>(out) + i, a.get());
   }
 }
 
@@ -378,13 +379,18 @@ struct VecTile {
                                   static_cast<char*>(bd->out_scale) +
                                   poff * kElemBytes)
                             : nullptr;
-    auto emit = [&](uint32_t v, const uint4(&xx)[P]) {
+    // row q: each rank's 1 KiB at a wave-uniform address, 16 bytes a lane
+    auto fetch = [&](uint32_t q, uint4(&xx)[P]) {
+#pragma unroll
+      for (int r = 0; r < P; ++r) xx[r] = ld_stream(in[r] + (size_t)q * 64u + lane);
+    };
+    auto emit = [&](uint32_t q, const uint4(&xx)[P]) {
       if constexpr (Kind == 3) {
         uint4 low;
-        st_stream(out + v, VecCombine<Acc, P, 3>::run(xx, low));
-        st_stream(out2 + v, low);
+        st_row(out + (size_t)q * 64u, lane, VecCombine<Acc, P, 3>::run(xx, low));
+        st_row(out2 + (size_t)q * 64u, lane, low);
       } else {
-        st_stream(out + v, VecCombine<Acc, P, Kind>::run(xx));
+        st_row(out + (size_t)q * 64u, lane, VecCombine<Acc, P, Kind>::run(xx));
       }
     };
     const uint32_t nv = (uint32_t)(plen / kPerVec);  // whole vectors
@@ -401,30 +407,23 @@ struct VecTile {
     for (; k + (U - 1) * nwaves < rows.limit; k += U * nwaves) {
       uint4 x[U][P];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u) fetch(rows.row(k + u * nwaves), x[u]);
 #pragma unroll
-        for (int r = 0; r < P; ++r)
-          x[u][r] = ld_stream(in[r] + rows.row(k + u * nwaves) * 64u + lane);
-#pragma unroll
-      for (int u = 0; u < U; ++u) emit(rows.row(k + u * nwaves) * 64u + lane, x[u]);
+      for (int u = 0; u < U; ++u) emit(rows.row(k + u * nwaves), x[u]);
     }
     for (; k < rows.limit; k += nwaves) {
       uint4 x[P];
-      const uint32_t v = rows.row(k) * 64u + lane;
-#pragma unroll
-      for (int r = 0; r < P; ++r) x[r] = ld_stream(in[r] + v);
-      emit(v, x);
+      fetch(rows.row(k), x);
+      emit(rows.row(k), x);
     }
     // the partition's ragged end: a partial row and the last < 16 bytes,
     // done by the tile that owns row `full`
     if (wave != 0 || full >= all || !owns_row(full, lt, nt, rpt, inter))
       return;
-    const uint32_t v = full * 64u + lane;
-    if (v < nv) {
+    if (full * 64u + lane < nv) {
       uint4 x[P];
-#pragma unroll
-      for (int r = 0; r < P; ++r) x[r] = ld_stream(in[r] + v);
-      emit(v, x);
+      fetch(full, x);
+      emit(full, x);
     }
     const uint32_t tail = (uint32_t)(plen - (uint64_t)nv * kPerVec);
     if (lane < tail) {
@@ -607,21 +606,23 @@ template <bool COMP, class Fmt>
 struct Fp8Tile {
   static constexpr uint32_t kRowElems = 1024;  // 64 lanes x 16 codes
 
-  // One row: lane `lane` owns codes el .. el + 16 of block blk.  FULL: the
+  // Row q: lane l owns codes el .. el + 16 of block blk.  FULL: the
   // whole row is inside the bucket (every lane has 16 codes), which spares
   // the per-lane length checks; otherwise `have` codes (0..16).
   template <int P, bool FULL>
   __device__ __forceinline__ static void row(const uint8_t* const (&in)[P],
                                              const float* const (&sc)[P],
                                              uint8_t* out, float* osc,
-                                             uint32_t el, uint32_t have) {
+                                             uint32_t q, uint32_t have) {
+    const uint32_t el = q * kRowElems + lane_id() * 16u;
     const uint32_t blk = el / 256u;
     uint4 raw[P];
     float s_in[P];
 #pragma unroll
     for (int r = 0; r < P; ++r) {
       if (FULL) {
-        raw[r] = ld_stream(reinterpret_cast<const uint4*>(in[r] + el));
+        raw[r] = ld_stream(reinterpret_cast<const uint4*>(
+                               in[r] + (size_t)q * kRowElems) + lane_id());
         s_in[r] = sc[r][blk];
       } else {
         raw[r] = have ? load_codes(in[r] + el, have) : make_uint4(0, 0, 0, 0);
@@ -684,13 +685,13 @@ struct Fp8Tile {
       w[k] = Fmt::enc4(y[4 * k] * inv, y[4 * k + 1] * inv, y[4 * k + 2] * inv,
                        y[4 * k + 3] * inv);
     if (FULL || have == 16u) {
-      st_stream(reinterpret_cast<uint4*>(out + el),
-                make_uint4(w[0], w[1], w[2], w[3]));
+      st_row(out + (size_t)q * kRowElems, lane_id(),
+             make_uint4(w[0], w[1], w[2], w[3]));
     } else if (have) {
       for (uint32_t j = 0; j < have; ++j)
-        out[el + j] = (uint8_t)(w[j >> 2] >> (8 * (j & 3)));
+        st_out(out + el + j, (uint8_t)(w[j >> 2] >> (8 * (j & 3))));
     }
-    if ((FULL || have) && (lane_id() & 15u) == 0u) osc[blk] = so;
+    if ((FULL || have) && (lane_id() & 15u) == 0u) st_out(osc + blk, so);
   }
 
   template <int P>
@@ -714,12 +715,12 @@ struct Fp8Tile {
     const RowSet rows(lt, nt, (nrows + nt - 1) / nt, inter, nrows);
     for (uint32_t k = wave; k < rows.limit; k += nwaves) {
       const uint32_t q = rows.row(k);
-      const uint32_t el = q * kRowElems + lane * 16u;
       if ((q + 1u) * kRowElems <= n) {  // uniform: the row is whole
-        row<P, true>(in, sc, out, osc, el, 16u);
+        row<P, true>(in, sc, out, osc, q, 16u);
       } else {
+        const uint32_t el = q * kRowElems + lane * 16u;
         const uint32_t have = el < n ? (n - el < 16u ? n - el : 16u) : 0u;
-        row<P, false>(in, sc, out, osc, el, have);
+        row<P, false>(in, sc, out, osc, q, have);
       }
     }
   }
@@ -822,14 +823,16 @@ struct MxTile {
   __device__ __forceinline__ static void row(const uint8_t* const (&in)[P],
                                              const uint8_t* const (&sc)[P],
                                              uint8_t* out, uint8_t* osc,
-                                             uint32_t el, uint32_t have) {
+                                             uint32_t q, uint32_t have) {
+    const uint32_t el = q * kRowElems + lane_id() * 16u;
     const uint32_t blk = el / 32u;
     uint4 raw[P];
     uint32_t b_in[P];
 #pragma unroll
     for (int r = 0; r < P; ++r) {
       if (FULL) {
-        raw[r] = ld_stream(reinterpret_cast<const uint4*>(in[r] + el));
+        raw[r] = ld_stream(reinterpret_cast<const uint4*>(
+                               in[r] + (size_t)q * kRowElems) + lane_id());
         b_in[r] = sc[r][blk];
       } else {
         raw[r] = have ? load_codes(in[r] + el, have) : make_uint4(0, 0, 0, 0);
@@ -902,13 +905,13 @@ struct MxTile {
     const uint32_t b = mx_scale_byte(amax);
     const uint4 codes = mx_enc16(y, e8m0_operand(b));
     if (FULL || have == 16u) {
-      st_stream(reinterpret_cast<uint4*>(out + el), codes);
+      st_row(out + (size_t)q * kRowElems, lane_id(), codes);
     } else if (have) {
       const uint32_t w[4] = {codes.x, codes.y, codes.z, codes.w};
       for (uint32_t j = 0; j < have; ++j)
-        out[el + j] = (uint8_t)(w[j >> 2] >> (8 * (j & 3)));
+        st_out(out + el + j, (uint8_t)(w[j >> 2] >> (8 * (j & 3))));
     }
-    if ((FULL || have) && (lane_id() & 1u) == 0u) osc[blk] = (uint8_t)b;
+    if ((FULL || have) && (lane_id() & 1u) == 0u) st_out(osc + blk, (uint8_t)b);
   }
 
   template <int P>
@@ -932,12 +935,12 @@ struct MxTile {
     const RowSet rows(lt, nt, (nrows + nt - 1) / nt, inter, nrows);
     for (uint32_t k = wave; k < rows.limit; k += nwaves) {
       const uint32_t q = rows.row(k);
-      const uint32_t el = q * kRowElems + lane * 16u;
       if ((q + 1u) * kRowElems <= n) {  // uniform: the row is whole
-        row<P, true>(in, sc, out, osc, el, 16u);
+        row<P, true>(in, sc, out, osc, q, 16u);
       } else {
+        const uint32_t el = q * kRowElems + lane * 16u;
         const uint32_t have = el < n ? (n - el < 16u ? n - el : 16u) : 0u;
-        row<P, false>(in, sc, out, osc, el, have);
+        row<P, false>(in, sc, out, osc, q, have);
       }
     }
   }
