@@ -8,8 +8,10 @@
 
 namespace pcoll {
 
-hipError_t launch_reduce(const ReduceArgs& a, int dtype, int op, bool comp,
-                         bool deep, int nranks, const Launch& l) {
+namespace {
+template <class Args>
+hipError_t dispatch(const Args& a, int dtype, int op, bool comp, bool deep,
+                    int nranks, const Launch& l) {
   if (nranks < 1 || nranks > kMaxRanks || l.groups < 1 || l.waves < 1 ||
       l.waves > kMaxWavesPerGroup)
     return hipErrorInvalidValue;
@@ -35,6 +37,18 @@ hipError_t launch_reduce(const ReduceArgs& a, int dtype, int op, bool comp,
     default:
       return hipErrorInvalidValue;
   }
+}
+
+}  // namespace
+
+hipError_t launch_reduce(const ReduceArgs& a, int dtype, int op, bool comp,
+                         bool deep, int nranks, const Launch& l) {
+  return dispatch(a, dtype, op, comp, deep, nranks, l);
+}
+
+hipError_t launch_reduce(const DirectArgs& a, int dtype, int op, bool comp,
+                         bool deep, int nranks, const Launch& l) {
+  return dispatch(a, dtype, op, comp, deep, nranks, l);
 }
 
 // ------------------------------------------------------------ ready signal

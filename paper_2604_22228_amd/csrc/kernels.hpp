@@ -48,6 +48,9 @@ struct Launch {
 // combination.
 hipError_t launch_reduce(const ReduceArgs& a, int dtype, int op, bool comp,
                          bool deep, int nranks, const Launch& l);
+// The direct kernel: l.groups = its tiles.  The same combinations.
+hipError_t launch_reduce(const DirectArgs& a, int dtype, int op, bool comp,
+                         bool deep, int nranks, const Launch& l);
 // Device-side readiness: appends `a.n` partition ids to the device ready
 // ring.
 hipError_t launch_pready(const PreadyArgs& a, hipStream_t s);

@@ -151,6 +151,19 @@ struct ReduceArgs {
                           // its last tile; tiles reduced), or null
 };
 
+// Arguments of the direct kernel (passed by value): one message, everything
+// ready.  It is cut into spans of `span` elements (one, or the partitions of
+// a message beyond 2^31 elements), each into tiles of at most `tile_rows`
+// rows; workgroup g reduces tile g % span_tiles of span g / span_tiles.
+struct DirectArgs {
+  BucketDesc bucket;
+  uint64_t span;
+  uint32_t span_tiles;  // tiles of a whole span
+  uint32_t tile_rows;
+  uint32_t row_shift;   // log2 of the elements per row
+  uint32_t interleave;  // tile layout, as in ReduceArgs
+};
+
 // Where a device-side ready signal appends: the rings of the request, and
 // the epoch the signal was enqueued in (fixed at enqueue time, so a signal
 // that runs late still names its own epoch).

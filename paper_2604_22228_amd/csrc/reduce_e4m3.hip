@@ -2,9 +2,15 @@
 #include "reduce_impl.hpp"
 
 namespace pcoll {
-hipError_t launch_reduce_e4m3(const ReduceArgs& a, bool comp, int nranks, const Launch& l) {
+template <class Args>
+hipError_t launch_reduce_e4m3(const Args& a, bool comp, int nranks, const Launch& l) {
   using namespace dev;
   if (comp) return launch_ranks<E4M3Tile<true>>(a, nranks, l);
   return launch_ranks<E4M3Tile<false>>(a, nranks, l);
 }
+
+template hipError_t launch_reduce_e4m3(const ReduceArgs&, bool, int,
+                                       const Launch&);
+template hipError_t launch_reduce_e4m3(const DirectArgs&, bool, int,
+                                       const Launch&);
 }  // namespace pcoll

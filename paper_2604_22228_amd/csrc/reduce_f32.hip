@@ -3,8 +3,8 @@
 
 namespace pcoll {
 namespace {
-template <bool D>
-hipError_t f32(const ReduceArgs& a, int op, bool comp, int nranks, const Launch& l) {
+template <bool D, class Args>
+hipError_t f32(const Args& a, int op, bool comp, int nranks, const Launch& l) {
   using namespace dev;
   if (op == kMax) return launch_ranks<VecTile<FMax, 0, D>>(a, nranks, l);
   if (comp) return launch_ranks<VecTile<FSum<true>, 0, D>>(a, nranks, l);
@@ -12,9 +12,15 @@ hipError_t f32(const ReduceArgs& a, int op, bool comp, int nranks, const Launch&
 }
 }  // namespace
 
-hipError_t launch_reduce_f32(const ReduceArgs& a, int op, bool comp, bool deep,
+template <class Args>
+hipError_t launch_reduce_f32(const Args& a, int op, bool comp, bool deep,
                              int nranks, const Launch& l) {
   return deep ? f32<true>(a, op, comp, nranks, l)
               : f32<false>(a, op, comp, nranks, l);
 }
+
+template hipError_t launch_reduce_f32(const ReduceArgs&, int, bool, bool,
+                                      int, const Launch&);
+template hipError_t launch_reduce_f32(const DirectArgs&, int, bool, bool,
+                                      int, const Launch&);
 }  // namespace pcoll

@@ -3,9 +3,15 @@
 #include "reduce_impl.hpp"
 
 namespace pcoll {
-hipError_t launch_reduce_mx(const ReduceArgs& a, bool comp, int nranks, const Launch& l) {
+template <class Args>
+hipError_t launch_reduce_mx(const Args& a, bool comp, int nranks, const Launch& l) {
   using namespace dev;
   if (comp) return launch_ranks<MxTile<true>>(a, nranks, l);
   return launch_ranks<MxTile<false>>(a, nranks, l);
 }
+
+template hipError_t launch_reduce_mx(const ReduceArgs&, bool, int,
+                                     const Launch&);
+template hipError_t launch_reduce_mx(const DirectArgs&, bool, int,
+                                     const Launch&);
 }  // namespace pcoll

@@ -360,8 +360,8 @@ struct VecTile {
   // Reduces wavefront `wave`'s rows of the tile: rows k = wave, wave +
   // nwaves, ... of the tile's row set; wavefront 0 also does the
   // partition's ragged end if this tile owns it.
-  template <int P>
-  __device__ __forceinline__ static void run(const_ptr<BucketDesc> bd,
+  template <int P, class Bucket>
+  __device__ __forceinline__ static void run(Bucket bd,
                                              uint64_t poff, uint64_t plen,
                                              uint32_t lt, uint32_t nt,
                                              uint32_t inter, uint32_t wave,
@@ -694,8 +694,8 @@ struct Fp8Tile {
     if ((FULL || have) && (lane_id() & 15u) == 0u) st_out(osc + blk, so);
   }
 
-  template <int P>
-  __device__ __forceinline__ static void run(const_ptr<BucketDesc> bd,
+  template <int P, class Bucket>
+  __device__ __forceinline__ static void run(Bucket bd,
                                              uint64_t poff, uint64_t plen,
                                              uint32_t lt, uint32_t nt,
                                              uint32_t inter, uint32_t wave,
@@ -914,8 +914,8 @@ struct MxTile {
     if ((FULL || have) && (lane_id() & 1u) == 0u) st_out(osc + blk, (uint8_t)b);
   }
 
-  template <int P>
-  __device__ __forceinline__ static void run(const_ptr<BucketDesc> bd,
+  template <int P, class Bucket>
+  __device__ __forceinline__ static void run(Bucket bd,
                                              uint64_t poff, uint64_t plen,
                                              uint32_t lt, uint32_t nt,
                                              uint32_t inter, uint32_t wave,
