@@ -10,7 +10,9 @@ rows in flight per lane) combination of its grid on seeded synthetic
 inputs and writes the fastest into the text table the library reads at
 request creation (tuned_mi355x.txt next to libpcoll.so, or
 PCOLL_TUNE_FILE).  Rows of one (dtype, op, ranks, graph) cover contiguous
-size ranges: each key's row reaches down to the next smaller key's.  The
+size ranges: each key's row reaches down to the next smaller key's, the
+smallest to a quarter of its size; what no row covers takes the library's
+rule.  The
 batched workloads are tuned for direct launches and for graph replays
 apart; a graph row is written before the direct one, whose graph column is
 "*" (it also serves graph replays of keys without a graph row of their
@@ -64,7 +66,10 @@ GROUPS_PER_CU_8BIT = (1, 2, 3)
 # consecutive rows per tile too: the rows that share a line of block
 # scales are then read by one workgroup
 INTERLEAVE_8BIT = (0, 1, 4, 8, 16)
-FALLBACK = "* * * * 0 63 8192 1 16 8 64 4"
+# a key's row covers sizes down to a quarter of it; from 2^24 bytes per rank
+# on the largest key's row also covers all larger sizes, else twice its size.
+# Other sizes, ranks and types take the library's rule (tuning.cpp)
+REACH_DOWN, ALL_FROM = 2, 24
 
 
 def grid_for(dtype, ranks=8):
@@ -81,8 +86,7 @@ def default_keys():
     partition counts whose mean time is scored)."""
     from paper_2604_22228_amd import synth
     keys = []
-    for k in range(10, 27, 2):  # the FP32 sweep, 4 KiB .. 256 MiB per rank
-        keys.append((1, 0, 8, 0, [1 << k], (1, 4, 16, 64)))
+    keys.append((1, 0, 8, 0, [1 << 26], (1, 4, 16, 64)))  # the FP32 sweep's top
     keys.append((1, 0, 4, 0, [262144], 8))          # plain workload
     keys.append((0, 0, 16, 0, [1 << 24], 256))      # int32 sum
     keys.append((0, 1, 16, 0, [1 << 24], 256))      # int32 max
@@ -212,8 +216,7 @@ def tune(keys, grid, warmup, reps, log=print):
 
 
 def read_table(path):
-    """The rows of an existing table (fallback excluded), in the form
-    tune() returns them, so that a partial run can keep the other keys."""
+    """The rows of an existing table, in the form tune() returns them, so that a partial run can keep the other keys."""
     rows = []
     with open(path) as f:
         for line in f:
@@ -231,7 +234,7 @@ def read_table(path):
 
 def write_table(rows, path):
     """One line per key; the keys of one (dtype, op, ranks, graph) cover
-    contiguous ranges of log2(bytes per rank), the largest up to 63."""
+    contiguous ranges of log2(bytes per rank)."""
     groups = {}
     for r in rows:
         groups.setdefault(r[:4], []).append(r)
@@ -245,13 +248,14 @@ def write_table(rows, path):
     keys = sorted(keys, key=lambda k: [kk[:3] for kk in groups].index(k[:3]))
     for key in keys:
         rs = sorted(groups[key], key=lambda r: r[4])
-        lo = 0
+        lo = max(0, rs[0][4] - REACH_DOWN)
         for i, (d, o, rk, g, lg, (t, gpc, il, w, b, u), ms) in enumerate(rs):
-            hi = 63 if i == len(rs) - 1 else lg
+            hi = lg
+            if i == len(rs) - 1:
+                hi = 63 if lg >= ALL_FROM else lg + 1
             lines.append(f"{d} {o} {rk} {g} {lo} {hi} {t} {gpc} {il} {w} {b}"
                          f" {u}   # {ms:.4f} at 2^{lg} B")
             lo = hi + 1
-    lines.append(FALLBACK + "   # fallback")
     with open(path, "w") as f:
         f.write("\n".join(lines) + "\n")
 

@@ -438,6 +438,7 @@ pcoll_config_t config_for(int dtype, int op, int nranks, uint64_t bytes) {
   // graph launch of one node costs more host time than a kernel launch
   c.graph = env_int("PCOLL_GRAPH", 0) ? 1 : 0;
   TuneChoice t = tune_lookup(tune_rows(), dtype, op, nranks, c.graph, bytes);
+  if (!t.matched) t = shape_rule(dtype, nranks, bytes);
   c.tile_elems = env_int("PCOLL_TILE", t.tile_elems);
   c.min_tile_elems = env_int("PCOLL_MIN_TILE", 4096);
   if (c.min_tile_elems > c.tile_elems) c.min_tile_elems = c.tile_elems;

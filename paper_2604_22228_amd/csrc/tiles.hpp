@@ -403,19 +403,22 @@ struct VecTile {
     constexpr int U0 = Unroll<P, DEEP>::value;
     constexpr bool kBf16Max = Kind == 2 && std::is_same<Acc, FMax>::value;
     constexpr int U = kBf16Max && U0 > 2 ? 2 : U0;
+    // U rows at a time, then U / 2, then one: whatever is left of a tile has
+    // as many loads in flight as it can
     uint32_t k = wave;
-    for (; k + (U - 1) * nwaves < rows.limit; k += U * nwaves) {
-      uint4 x[U][P];
+    auto batch = [&](auto depth) {
+      constexpr int D = decltype(depth)::value;
+      for (; k + (D - 1) * nwaves < rows.limit; k += D * nwaves) {
+        uint4 x[D][P];
 #pragma unroll
-      for (int u = 0; u < U; ++u) fetch(rows.row(k + u * nwaves), x[u]);
+        for (int u = 0; u < D; ++u) fetch(rows.row(k + u * nwaves), x[u]);
 #pragma unroll
-      for (int u = 0; u < U; ++u) emit(rows.row(k + u * nwaves), x[u]);
-    }
-    for (; k < rows.limit; k += nwaves) {
-      uint4 x[P];
-      fetch(rows.row(k), x);
-      emit(rows.row(k), x);
-    }
+        for (int u = 0; u < D; ++u) emit(rows.row(k + u * nwaves), x[u]);
+      }
+    };
+    batch(std::integral_constant<int, U>{});
+    if constexpr (U > 2) batch(std::integral_constant<int, U / 2>{});
+    if constexpr (U > 1) batch(std::integral_constant<int, 1>{});
     // the partition's ragged end: a partial row and the last < 16 bytes,
     // done by the tile that owns row `full`
     if (wave != 0 || full >= all || !owns_row(full, lt, nt, rpt, inter))

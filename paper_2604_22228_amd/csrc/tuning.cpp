@@ -98,13 +98,52 @@ TuneChoice tune_lookup(const std::vector<TuneRow>& rows, int dtype, int op,
     if (match(r.dtype, dtype) && match(r.op, op) && match(r.ranks, ranks) &&
         match(r.graph, graph) && lg >= r.log2_lo && lg <= r.log2_hi)
       return {r.tile_elems, r.groups_per_cu, r.interleave, r.group_waves,
-              r.publish_batch, r.unroll};
+              r.publish_batch, r.unroll, true};
   }
   // built-in default: 16 KiB of output per tile, two groups per CU
   // (element bytes: 2 for bf16 and bf16 pairs, 1 for the 8-bit floats)
   const int elem = dtype == 2 || dtype == 6 ? 2
                                             : (dtype >= 3 && dtype <= 5 ? 1 : 4);
   return {16384 / elem, 2, 0, 4, 16, 4};
+}
+
+// Rows are 1 KiB of each rank.  A tile costs its group about 4 us of
+// latency, and all groups claim tiles from one counter, which gives out 60 a
+// microsecond: tiles want many bytes, the more rows the fewer ranks.  Beyond
+// that small tiles are better, since the tiles reduced at the same time then
+// stay close together in every rank's memory and the last ones end together.
+// Microseconds per epoch at 16 / 32 / 64 rows per tile:
+//   fp32   1 rank  2^26 elements  264 / 126 /  97     4 ranks 2^26  305 / 232 / 224
+//   fp32   2 ranks 2^26           273 / 149 / 138     3 ranks 2^25  132 /  96 / 102
+//   fp32   8 ranks 2^24           106 / 109 / 118    16 ranks 2^22   63 /  65 /  66
+//   bf16   2 ranks 2^27           273 / 148 / 137     4 ranks 2^26  141 / 116 / 125
+//   bf16   8 ranks 2^24            65 /  67 /  68
+//   e4m3   2 ranks 2^28           276 / 177 / 174     4 ranks 2^27  148 / 138 / 147
+//   e4m3   8 ranks 2^26           134 / 141 / 138     8 ranks 2^23   36 /  35 /  44
+// A message of fewer than 64 (8-bit: 128) such tiles gets smaller ones, down
+// to a row per wavefront, so that it is read by more compute units at once:
+// fp32, 8 ranks, 2^18 elements, 8 / 16 / 32 rows 17.1 / 16.2 / 19.0 us; e4m3,
+// 8 ranks, 2^20, 4 / 8 / 16 / 32 rows 21.9 / 20.3 / 22.5 / 28.2 us.
+//
+// One group of 8 wavefronts per compute unit (fp32 8 ranks 2^24: 106 against
+// 117 us with two), two where arithmetic must hide behind the loads of
+// others (8-bit: e4m3 2 ranks 2^28 174 against 217 us).  Rows in flight per
+// lane: as many as a wavefront has in a tile, at most 2 from 5 ranks on (6
+// ranks 2^26: 304 against 307 us).
+TuneChoice shape_rule(int dtype, int ranks, uint64_t bytes_per_rank) {
+  const bool bits8 = dtype >= 3 && dtype <= 5;
+  const uint64_t rows = (bytes_per_rank + 1023) / 1024;
+  uint64_t tile;
+  if (bits8)
+    tile = ranks <= 6 || rows <= 16384 ? 32 : 16;
+  else
+    tile = ranks <= 2 ? 64 : (ranks <= 6 ? 32 : 16);
+  uint64_t fit = rows / (bits8 ? 128 : 64) / 8 * 8;
+  if (fit < 8) fit = 8;
+  if (tile > fit) tile = fit;
+  const int row_elems = bits8 ? 1024 : (dtype == 2 || dtype == 6 ? 512 : 256);
+  return {(int)tile * row_elems, bits8 ? 2 : 1, bits8 ? 0 : 8, 8, 64,
+          ranks >= 5 && ranks <= 8 ? 2 : 4, false};
 }
 
 }  // namespace pcoll

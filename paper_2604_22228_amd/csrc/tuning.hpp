@@ -38,6 +38,7 @@ struct TuneChoice {
   int group_waves;
   int publish_batch;
   int unroll;
+  bool matched = false;  // a row of the table matched
 };
 
 // Parses a table; malformed lines are skipped.  Returns the rows.
@@ -46,5 +47,9 @@ std::vector<TuneRow> parse_tune_table(const std::string& text);
 // First matching row, or the built-in default.
 TuneChoice tune_lookup(const std::vector<TuneRow>& rows, int dtype, int op,
                        int ranks, int graph, uint64_t bytes_per_rank);
+
+// The launch shape where the table has no row: from the payload type, the
+// ranks and the size alone.
+TuneChoice shape_rule(int dtype, int ranks, uint64_t bytes_per_rank);
 
 }  // namespace pcoll
