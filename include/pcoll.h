@@ -273,10 +273,10 @@ int pcoll_pready_rank_on_stream(pcoll_req_t req, int rank,
  * output is final in the current (or last completed) epoch.  PCOLL_ERR_STATE before the first
  * start.  Arrival (Section 4.5: a partition counts only after all of its
  * chunks have landed) is signalled by the partition's own flag, which the
- * kernel sets once it has published the partition's last tile; the
- * retirement of the epoch's kernel with no error implies every partition.
- * For a partition whose flag is not set yet the call costs one
- * hipEventQuery. */
+ * kernel sets as it publishes the partition's last tile, or for the tiles
+ * that its workgroups hold when the work runs out (config field
+ * publish_batch) by the epoch's completion as a whole.  While the partition
+ * has not arrived the call costs one hipEventQuery. */
 int pcoll_parrived(pcoll_req_t req, int part, int *flag);
 
 /* Non-blocking test of the whole epoch (MPI_Test): *flag = 1 once every
@@ -355,9 +355,10 @@ typedef struct {
                         tile's rows */
   int publish_batch; /* finished tiles a workgroup publishes at once
                         (1..64).  A workgroup also publishes before it waits
-                        for readied work and when it runs out of work, so
-                        the batch only delays arrival flags while the kernel
-                        has a backlog: larger lets a workgroup's wavefronts
+                        for readied work (the tiles it holds when the work
+                        runs out complete with the epoch), so the batch only
+                        delays arrival flags while the kernel has a backlog:
+                        larger lets a workgroup's wavefronts
                         run on without waiting for their stores, smaller
                         lets partitions arrive sooner under backlog */
   int guide;         /* guided self-scheduling divisor f (0..64): a

@@ -18,6 +18,9 @@ namespace pcoll {
 
 constexpr int kMaxRanks = 16;
 constexpr int kMaxPublishBatch = 64;
+// Atomics on one address take 16 ns each, one after the other: 256 workgroups
+// that end together count in two steps of at most 16 or so.
+constexpr uint32_t kRetireSets = 16;
 
 // Per bucket, in device memory; written once at bind time, read-only to the
 // kernels.
@@ -52,7 +55,9 @@ struct HostShared {
   uint32_t abort;         // host: == epoch asks the kernel to give up
   uint32_t status;        // device: error code of epoch status_epoch
   uint32_t status_epoch;  // device: epoch the status belongs to
-  uint32_t reserved[28];
+  uint32_t pad0[12];
+  uint32_t done;          // device: the last epoch whose every tile is final
+  uint32_t pad1[15];      // (on a line of its own: the host spins on it)
 };
 
 // Device-memory counters of one epoch, each group on its own 128-B line so
@@ -72,7 +77,13 @@ struct EpochCounters {
                                   // (guided tile sizes only)
   uint32_t pad1[26];
   uint32_t error;                 // first error seen this epoch
-  uint32_t pad3[31];
+  uint32_t pad2[31];
+  // workgroups that ran out of work: kRetireSets counters, and how many of
+  // them are full
+  struct {
+    uint32_t n;
+    uint32_t pad[31];
+  } retired[kRetireSets + 1];
 };
 
 // The ingest lock is part of the queue state: one compare-and-swap takes it

@@ -35,7 +35,7 @@
 // Exit: t >= total tiles.  A worker that starves past the deadline, or sees
 // the host's abort word, records the reason (also in host memory, stamped
 // with the epoch) and leaves; the others follow.  The host's wait returns
-// when every arrived flag carries the epoch, or an error is recorded (or the
+// when the done word carries the epoch, or an error is recorded (or the
 // launch has failed).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -589,8 +589,12 @@ __device__ __forceinline__ void locate(const ReduceArgs& a, uint32_t t,
 // wavefront waits for its stores once (kJobDrain), then one instruction counts
 // the tiles, a lane each.  It does so when the batch is full, before it waits
 // for work (a partition is late by at most one batch of one group, and only
-// while the kernel has a backlog of readied work), and when it runs out of
-// work, so that the host sees the last partitions arrive without waiting for
+// while the kernel has a backlog of readied work).
+//
+// A group that runs out of work counts itself instead (retire): when the last
+// one has, every tile of the epoch is final, and it stores the epoch into the
+// host's done word.  That is one bus write, not one per partition (256
+// partitions of a small message: 28 -> 19 us), and the host does not wait for
 // the launch to retire and its end event to be processed.
 //
 // Measured: with ordinary stores, each publication wrote back the XCD's L2
@@ -625,6 +629,31 @@ __device__ __forceinline__ void publish(const ReduceArgs& a,
   npend = 0;
 }
 
+// The group has run out of work, and its stores are in memory: its pending
+// tiles need no counts of their own.
+__device__ __forceinline__ void retire(const ReduceArgs& a,
+                                       const Pending* pend, uint32_t npend,
+                                       uint32_t epoch) {
+  const uint32_t l = lane_id();
+  if (a.tile_hits && l < npend)
+    __hip_atomic_fetch_add(&a.tile_hits[pend[l].part], 1u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+  if (l != 0) return;
+  const uint32_t set = blockIdx.x % kRetireSets;
+  const uint32_t members = (a.total_groups - set + kRetireSets - 1) / kRetireSets;
+  const uint32_t sets = min(a.total_groups, kRetireSets);
+  if (__hip_atomic_fetch_add(&a.ctr->retired[set].n, 1u, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT) +
+              1u ==
+          members &&
+      __hip_atomic_fetch_add(&a.ctr->retired[kRetireSets].n, 1u,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+              1u ==
+          sets)
+    __hip_atomic_store(&a.host->done, epoch, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The tile index after the first round: one relaxed atomic add by lane 0.
 __device__ __forceinline__ uint32_t claim(const ReduceArgs& a) {
   uint32_t t = 0;
@@ -636,10 +665,11 @@ __device__ __forceinline__ uint32_t claim(const ReduceArgs& a) {
 }
 
 // What wavefront 0 hands the group: one tile, or
-constexpr uint32_t kJobStop = ~0u;        // the end
-constexpr uint32_t kJobDrain = ~0u - 1u;  // wait for your stores
+constexpr uint32_t kJobStop = ~0u;         // the end
+constexpr uint32_t kJobDrain = ~0u - 1u;   // wait for your stores
+constexpr uint32_t kJobRetire = ~0u - 2u;  // the same, and the end
 struct TileJob {
-  uint32_t part;  // global partition, or one of the two above
+  uint32_t part;  // global partition, or one of the above
   uint32_t lt;    // tile index within the partition
   uint32_t nt;    // tiles of the partition
 };
@@ -672,6 +702,7 @@ __device__ __forceinline__ void clear_next_epoch(const ReduceArgs& args,
     st_rlx64(&c->consumed, 0ull);
     st_rlx64(&c->queued_rows, 0ull);
     st_rlx(&c->error, 0u);
+    for (uint32_t k = 0; k <= kRetireSets; ++k) st_rlx(&c->retired[k].n, 0u);
     st_rlx64(&args.ring[other].reserve, (uint64_t)next_epoch(epoch) << 32);
   }
 }
@@ -729,9 +760,10 @@ __device__ __forceinline__ void persistent_loop(const ReduceArgs& args) {
         j.lt = t - at.prev_end;
         j.nt = at.end - at.prev_end;
         next = claim(a);  // in flight while the tile is reduced
-      } else if (w == kDrain || (w == kStop && npend != 0u)) {
-        j.part = kJobDrain;
-      } else if (a.trace && lane_id() == 0) {
+      } else if (w != kBail) {
+        j.part = w == kStop ? kJobRetire : kJobDrain;
+      }
+      if (a.trace && (w == kStop || w == kBail) && lane_id() == 0) {
         uint64_t* s = a.trace + (size_t)blockIdx.x * 4u;
         s[0] = t0;
         s[1] = t_first;
@@ -743,9 +775,13 @@ __device__ __forceinline__ void persistent_loop(const ReduceArgs& args) {
     __syncthreads();
     const TileJob j = jobs[turn];
     if (j.part == kJobStop) break;
-    if (j.part == kJobDrain) {
+    if (j.part >= kJobRetire) {  // retire or drain
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
+      if (j.part == kJobRetire) {
+        if (wave == 0) retire(a, pend, npend, epoch);
+        break;
+      }
       if (wave == 0) publish(a, pend, npend, epoch);
       continue;
     }

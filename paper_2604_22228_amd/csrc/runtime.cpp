@@ -6,8 +6,9 @@
 //   * host-coherent pinned memory (HostShared + ready list + arrived flags)
 //     is the channel between the host thread and the running kernel:
 //     pready appends epoch-tagged entries to the ready list; the kernel
-//     stores arrived[p] = epoch when partition p is final, and an epoch-stamped status if it gives up; the host's wait
-//     returns once every arrived flag carries the epoch;
+//     stores arrived[p] = epoch as it publishes partition p's last tile, the
+//     done word once every tile of the epoch is final, and an epoch-stamped
+//     status if it gives up; the host's wait returns on the done word;
 //   * device memory holds the work queue and the counters the kernel's
 //     wavefronts share;
 //   * an LRU cache (Section 4.2's graph cache) maps each binding to its
@@ -202,7 +203,6 @@ struct pcoll_req_s {
   uint32_t epoch = 0;
   bool active = false;
   bool epoch_ok = false;        // the last finished epoch completed
-  uint32_t scan = 0;            // first partition not yet seen arrived
   uint32_t hcount = 0;
   std::vector<uint32_t> stamp;  // epoch in which each partition was readied
   std::vector<uint64_t> mark;   // call generation that last listed it
@@ -262,6 +262,7 @@ int reset_epoch_state(pcoll_req_t r, uint32_t last) {
   std::memset(r->arrived, 0, sizeof(uint32_t) * np);
   r->host->status = 0;
   r->host->status_epoch = 0;
+  r->host->done = 0;
   std::fill(r->stamp.begin(), r->stamp.end(), 0u);
   std::fill(r->rank_epoch.begin(), r->rank_epoch.end(), 0u);
   std::fill(r->rank_mask.begin(), r->rank_mask.end(), 0u);
@@ -736,14 +737,9 @@ uint32_t epoch_status(const pcoll_req_s* r) {
   return __atomic_load_n(&r->host->status, __ATOMIC_RELAXED);
 }
 
-// Whether every partition has arrived this epoch by its flag; `scan`
-// remembers the first one not seen arrived, so a wait reads each flag
-// about once.
-bool all_arrived(pcoll_req_s* r) {
-  while (r->scan < r->nparts_total &&
-         __atomic_load_n(&r->arrived[r->scan], __ATOMIC_ACQUIRE) == r->epoch)
-    ++r->scan;
-  return r->scan == r->nparts_total;
+// Whether every tile of the epoch is final, by the kernel's done word.
+bool all_arrived(const pcoll_req_s* r) {
+  return __atomic_load_n(&r->host->done, __ATOMIC_ACQUIRE) == r->epoch;
 }
 
 // Whether the epoch's launch has retired: 1 yes, 0 not yet, or a negative
@@ -798,7 +794,7 @@ int complete_ok(pcoll_req_t r) {
 }
 
 // One look at the epoch: 1 complete (then finished), 0 not yet, or a
-// negative error code.  The arrived flags are read every time; the launch's
+// negative error code.  The done word is read every time; the launch's
 // retirement, which costs a runtime call, only with query_event.
 int poll_epoch(pcoll_req_t r, bool query_event) {
   if (all_arrived(r)) return complete_ok(r);
@@ -824,7 +820,7 @@ int spin_wait(pcoll_req_t r, int limit_ms) {
   auto t0 = std::chrono::steady_clock::now();
   bool aborted = false;
   for (uint64_t it = 0;; ++it) {
-    // every partition's arrival and every error of the kernel show in the
+    // the epoch's completion and every error of the kernel show in the
     // pinned block; the event, whose query costs a microsecond of runtime
     // calls, only tells of a launch that failed
     const int rc = poll_epoch(r, (it & 1023) == 1023);
@@ -1022,7 +1018,6 @@ int pcoll_start(pcoll_req_t r) {
   r->host->abort = 0;
   __atomic_store_n(&r->host->epoch, e, __ATOMIC_RELEASE);
   r->hcount = 0;
-  r->scan = 0;
   hipEvent_t* tp = r->cfg.debug ? r->ev_t[r->t_next] : nullptr;
   if (r->cfg.debug & 1) {
     HIP_TRY(hipMemsetAsync(r->d_hits, 0, sizeof(uint32_t) * r->nparts_total,
@@ -1208,6 +1203,10 @@ int pcoll_parrived(pcoll_req_t r, int part, int* flag) {
   }
   if (!r->active) {
     *flag = r->epoch_ok ? 1 : 0;
+    return PCOLL_SUCCESS;
+  }
+  if (all_arrived(r)) {
+    *flag = 1;
     return PCOLL_SUCCESS;
   }
   // a launch that retired cleanly has completed every partition
