@@ -1321,11 +1321,17 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
   const uint64_t span_rows = (a.span + re - 1) / re;
   const uint64_t total_rows = (count + re - 1) / re;
   a.tile_rows = direct_tile_rows(dtype, total_rows);
-  a.span_tiles = (uint32_t)((span_rows + a.tile_rows - 1) / a.tile_rows);
+  uint64_t groups;
+  for (;; a.tile_rows *= 2u) {
+    a.span_tiles = (uint32_t)((span_rows + a.tile_rows - 1) / a.tile_rows);
+    groups = spans * a.span_tiles;
+    // a grid has fewer than 2^32 threads: larger tiles for what would need
+    // more (64 GiB a rank in bf16 and the 8-bit types, 128 GiB in 4-byte
+    // ones); one tile a span always fits
+    if (groups * (64u * kDirectWaves) < (1ull << 32)) break;
+  }
   a.row_shift = (uint32_t)__builtin_ctzll(re);
   a.interleave = kDirectBand;
-  const uint64_t groups = spans * a.span_tiles;
-  if (groups > 0x7fffffffull) return PCOLL_ERR_UNSUPPORTED;
   const Launch l{(int)groups, kDirectWaves, static_cast<hipStream_t>(stream),
                  nullptr, nullptr};
   HIP_TRY(launch_reduce(a, dtype, op, c.comp != 0, c.unroll != 2, nranks, l));
@@ -1480,9 +1486,9 @@ int pcoll_probe_stream(const void* const* srcs, int nsrc, void* dst,
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount,
                                   dev));
     if (layout == 1) {
-      // the headline reduce's tile schedule: tiles of 32 rows (8192
-      // binary32 elements), bands of 16 tiles, 2 workgroups of 8 waves per
-      // compute unit
+      // a tile schedule like the reduce's: tiles of 32 rows (8192 binary32
+      // elements), bands of 16 tiles, 2 workgroups of 8 waves per compute
+      // unit
       t.groups = (uint32_t)(2 * std::max(cus, 1));
       t.waves = 8;
       t.tile_rows = 32;

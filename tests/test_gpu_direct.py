@@ -68,6 +68,26 @@ def test_direct_beyond_2_31_elements():
     assert torch.equal(x, y)
 
 
+def test_direct_beyond_2_32_threads():
+    # 2^24 tiles of the usual 2048 elements would be a grid of 2^32 threads
+    n, step = (1 << 35) + 4096 * 3 + 5, 1 << 27
+    if torch.cuda.mem_get_info(DEV)[0] < 4 * n + (8 << 30):
+        pytest.skip("needs 136 GiB of device memory")
+    say(f"case direct n={n}")
+    base = torch.randint(0, 0x4000, (step,), dtype=torch.int16, device=DEV)
+    x = torch.empty(n, dtype=torch.int16, device=DEV)
+    y = torch.zeros_like(x)
+    for k, at in enumerate(range(0, n, step)):
+        torch.bitwise_xor(base[:min(step, n - at)], k, out=x[at:at + step])
+    pc.pcoll_reduce_noalloc(n, pc.BFLOAT16, pc.MAX, 33, [x], y, None, None,
+                            torch.cuda.current_stream(DEV))
+    torch.cuda.synchronize()
+    for at in range(0, n, step):
+        assert torch.equal(x[at:at + step], y[at:at + step]), at
+    del x, y
+    torch.cuda.empty_cache()
+
+
 def test_direct_calls_overlap_and_replay():
     P, n = 4, 3_000_001
     streams = [torch.cuda.Stream(DEV) for _ in range(2)]
