@@ -587,9 +587,13 @@ __device__ __forceinline__ void locate(const ReduceArgs& a, uint32_t t,
 // keeps up to `publish_batch` finished tiles pending, its wavefronts running
 // on into the next tiles with the stores still in flight; to publish, every
 // wavefront waits for its stores once (kJobDrain), then one instruction counts
-// the tiles, a lane each.  It does so when the batch is full, before it waits
-// for work (a partition is late by at most one batch of one group, and only
-// while the kernel has a backlog of readied work).
+// the tiles, a lane for each partition among them.  It does so when the batch
+// is full, before it waits for work (a partition is late by at most one batch
+// of one group, and only while the kernel has a backlog of readied work).  A
+// lane for each tile would put 64 atomics of every group on one counter where
+// a partition is large, at 16 ns each: fp32, 8 ranks, 256 MiB each, 1 / 4 / 16
+// partitions 480 / 450 / 436 us that way against 375 now (64 partitions 363
+// either way), 512 MiB in one partition 732 us.
 //
 // A group that runs out of work counts itself instead (retire): when the last
 // one has, every tile of the epoch is final, and it stores the epoch into the
@@ -612,16 +616,25 @@ __device__ __forceinline__ void publish(const ReduceArgs& a,
                                         uint32_t epoch) {
   if (npend == 0) return;
   const uint32_t l = lane_id();
-  if (l < npend) {
-    const uint32_t part = pend[l].part, nt = pend[l].nt;
-    if (a.tile_hits)
-      __hip_atomic_fetch_add(&a.tile_hits[part], 1u, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
+  const bool in = l < npend;
+  const uint32_t part = in ? pend[l].part : 0u;
+  // a group's tiles of one partition follow each other: the first of them
+  // counts them all
+  const bool head = in && (l == 0u || pend[l - 1u].part != part);
+  const uint64_t heads = __ballot(head);
+  if (in && a.tile_hits)
+    __hip_atomic_fetch_add(&a.tile_hits[part], 1u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+  if (head) {
+    const uint64_t later = heads & ~((2ull << l) - 1ull);
+    const uint32_t n =
+        (later ? (uint32_t)__ffsll((long long)later) - 1u : npend) - l;
+    const uint32_t nt = pend[l].nt;
     // exactly one add completes a partition; one of one tile needs no count
     if (nt == 1u ||
-        __hip_atomic_fetch_add(&a.done[part], 1u, __ATOMIC_RELAXED,
+        __hip_atomic_fetch_add(&a.done[part], n, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT) +
-                1u ==
+                n ==
             nt)
       __hip_atomic_store(&a.arrived[part], epoch, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_SYSTEM);
