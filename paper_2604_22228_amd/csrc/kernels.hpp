@@ -40,6 +40,7 @@ struct Launch {
   hipEvent_t start;
   hipEvent_t stop;
   int* per_cu = nullptr;
+  unsigned lds = 0;  // reduce_direct: reserved per workgroup, never used
 };
 
 // The persistent partitioned-reduce kernel; deep: 4 rows per lane in

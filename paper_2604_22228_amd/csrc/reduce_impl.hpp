@@ -45,7 +45,8 @@ hipError_t launch_ranks(const DirectArgs& a, int nranks, const Launch& l) {
   switch (nranks) {
 #define PCOLL_CASE(P)                                                      \
   case P:                                                                  \
-    hipLaunchKernelGGL((reduce_direct<Tile, P>), grid, block, 0, l.stream, a); \
+    hipLaunchKernelGGL((reduce_direct<Tile, P>), grid, block, l.lds, l.stream, \
+                       a);                                                 \
     break;
     PCOLL_CASE(1) PCOLL_CASE(2) PCOLL_CASE(3) PCOLL_CASE(4)
     PCOLL_CASE(5) PCOLL_CASE(6) PCOLL_CASE(7) PCOLL_CASE(8)

@@ -482,10 +482,28 @@ pcoll_config_t default_config(const pcoll_req_s* r) {
 // kernel's tiles, 32 rows by 8 wavefronts: 9.7, 406, 8.4, 205, 32.2 us.)  Bands
 // of 8 tiles: up to 2 % over consecutive rows from 64 MiB per rank on, no
 // difference below.
+//
+// Large messages of many streams run best with two of these workgroups per
+// compute unit, not the four that the registers allow: fewer places of each
+// buffer are open in memory at once.  Reserving LDS that nothing uses keeps it
+// at two; then 8 rows per tile and bands of 16.  Four / two workgroups: fp32,
+// 8 ranks, 256 MiB each 398 / 364 us (6.6 TB/s), 64 MiB 102 / 97 us, 4 ranks
+// 128 MiB 112 / 103 us; 12 ranks 128 MiB 297 / 266 us; bf16, 8 ranks, 32 MiB
+// 55 / 51 us; int32, 16 ranks, 16 MiB 55 / 52 us.  No gain below 128 MiB of
+// inputs (fp32, 8 ranks, 16 MiB: 27.6 / 27.7 us), a loss with fewer streams
+// (fp32, 1 rank, 128 MiB: 44 / 56 us) and for the 8-bit types, which need the
+// wavefronts for their arithmetic (e4m3 110 / 135 us).
 constexpr int kDirectWaves = 4;
-constexpr uint32_t kDirectBand = 8;
-uint32_t direct_tile_rows(int dtype, uint64_t rows) {
-  return elem_bytes(dtype) == 4 && rows >= 4096u ? 8u : 4u;
+struct DirectShape {
+  uint32_t rows;  // per tile
+  uint32_t band;
+  unsigned lds;
+};
+DirectShape direct_shape(int dtype, int nranks, uint64_t count, uint64_t rows) {
+  const uint64_t bytes = count * (uint64_t)elem_bytes(dtype) * (uint64_t)nranks;
+  if (!is_fp8(dtype) && nranks >= 4 && bytes >= (1ull << 27))
+    return {8u, 16u, 64000u};
+  return {elem_bytes(dtype) == 4 && rows >= 4096u ? 8u : 4u, 8u, 0u};
 }
 
 void destroy(pcoll_req_t r) {
@@ -1320,7 +1338,8 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
   const uint64_t spans = (count + a.span - 1) / a.span;
   const uint64_t span_rows = (a.span + re - 1) / re;
   const uint64_t total_rows = (count + re - 1) / re;
-  a.tile_rows = direct_tile_rows(dtype, total_rows);
+  const DirectShape shape = direct_shape(dtype, nranks, count, total_rows);
+  a.tile_rows = shape.rows;
   uint64_t groups;
   for (;; a.tile_rows *= 2u) {
     a.span_tiles = (uint32_t)((span_rows + a.tile_rows - 1) / a.tile_rows);
@@ -1331,9 +1350,9 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
     if (groups * (64u * kDirectWaves) < (1ull << 32)) break;
   }
   a.row_shift = (uint32_t)__builtin_ctzll(re);
-  a.interleave = kDirectBand;
+  a.interleave = shape.band;
   const Launch l{(int)groups, kDirectWaves, static_cast<hipStream_t>(stream),
-                 nullptr, nullptr};
+                 nullptr, nullptr, nullptr, shape.lds};
   HIP_TRY(launch_reduce(a, dtype, op, c.comp != 0, c.unroll != 2, nranks, l));
   return PCOLL_SUCCESS;
 }

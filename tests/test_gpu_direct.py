@@ -56,6 +56,28 @@ def test_direct_edges(dtype, rows):
             assert torch.equal(outs[0][1], outs[1][1])
 
 
+@pytest.mark.parametrize("dtype,P", [(pc.FLOAT32, 4), (pc.FLOAT32, 8),
+                                     (pc.FLOAT32, 3), (pc.BFLOAT16, 16)])
+@pytest.mark.parametrize("past", [-1, 0, 131])
+def test_direct_large_shape(dtype, P, past):
+    # 128 MiB of inputs, where the launch shape changes
+    stream = torch.cuda.current_stream(DEV)
+    n = (1 << 27) // (P * (2 if dtype == pc.BFLOAT16 else 4)) + past
+    say(f"case direct large dtype={dtype} P={P} n={n}")
+    bufs, _ = _inputs(dtype, P, n, P)
+    outs = [torch.full_like(bufs[0], 3) for _ in range(2)]
+    pc.pcoll_reduce_noalloc(n, dtype, pc.SUM, 5, bufs, outs[0], None, None,
+                            stream)
+    req = new_request([n], dtype, pc.SUM, 5, P)
+    req.bind([bufs], [outs[1]], stream=stream)
+    req.start()
+    req.pready_range(0, 4)
+    req.wait()
+    req.free()
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.uint8), outs[1].view(torch.uint8))
+
+
 def test_direct_beyond_2_31_elements():
     n = (1 << 31) + 4096 * 3 + 5
     say(f"case direct n={n}")
