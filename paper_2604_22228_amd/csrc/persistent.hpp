@@ -828,6 +828,16 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 v) {
   __builtin_nontemporal_store(w, (gstore_ptr)(p));
 }
 
+// Lane's 16 bytes of the 1 KiB row at `row` (wave-uniform), through a buffer
+// descriptor: the row's address stays in scalar registers.
+__device__ __forceinline__ uint4 ld_row(const void* row, uint32_t lane) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(row), 0, 1024, 0x00027000);
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(
+      rs, (int)(lane * 16u), 0, /* nt */ 2);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // Stores of a tile's results.  They go through to memory (the agent-scope
 // bit beside the nontemporal hint) instead of staying dirty in this XCD's L2:
 // once a wavefront has waited for them they are visible device-wide, and

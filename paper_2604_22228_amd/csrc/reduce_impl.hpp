@@ -12,7 +12,8 @@
 namespace pcoll {
 
 template <class Tile, int P>
-__global__ __launch_bounds__(64 * kMaxWavesPerGroup) void reduce_persistent(
+__global__ __launch_bounds__(64 * kMaxWavesPerGroup, (Tile::template waves<P>()))
+void reduce_persistent(
     ReduceArgs a) {
   dev::persistent_loop<Tile, P>(a);
 }
@@ -22,7 +23,8 @@ __global__ __launch_bounds__(64 * kMaxWavesPerGroup) void reduce_persistent(
 // has room.  No queue, no readiness, no completion beyond the launch's own,
 // so no state besides the arguments.
 template <class Tile, int P>
-__global__ __launch_bounds__(64 * kMaxWavesPerGroup) void reduce_direct(
+__global__ __launch_bounds__(64 * kMaxWavesPerGroup, (Tile::template waves<P>()))
+void reduce_direct(
     DirectArgs a) {
   const uint32_t wave = dev::uni(threadIdx.x / 64u);
   const uint32_t s = blockIdx.x / a.span_tiles;

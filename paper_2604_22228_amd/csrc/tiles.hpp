@@ -124,6 +124,16 @@ __device__ __forceinline__ float clamp_abs(float v, float m) {
 
 struct Fp8E4M3 {
   static constexpr float kMax = 448.0f;
+  static constexpr float kQuantum = 0x1p-9f;  // every value is a multiple
+  __device__ __forceinline__ static float dec(uint32_t w) {  // its low byte
+    return __builtin_amdgcn_cvt_f32_fp8((int)w, 0);
+  }
+  // four values that round to at most kMax
+  __device__ __forceinline__ static uint32_t enc4_small(float a, float b,
+                                                        float c, float d) {
+    const int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
+  }
   template <bool HI>
   __device__ __forceinline__ static auto dec_pair(uint32_t w) {
     return __builtin_amdgcn_cvt_pk_f32_fp8((int)w, HI);
@@ -139,6 +149,15 @@ struct Fp8E4M3 {
 };
 struct Fp8E5M2 {
   static constexpr float kMax = 57344.0f;
+  static constexpr float kQuantum = 0x1p-16f;
+  __device__ __forceinline__ static float dec(uint32_t w) {
+    return __builtin_amdgcn_cvt_f32_bf8((int)w, 0);
+  }
+  __device__ __forceinline__ static uint32_t enc4_small(float a, float b,
+                                                        float c, float d) {
+    const int w = __builtin_amdgcn_cvt_pk_bf8_f32(a, b, 0, false);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_bf8_f32(c, d, w, true);
+  }
   template <bool HI>
   __device__ __forceinline__ static auto dec_pair(uint32_t w) {
     return __builtin_amdgcn_cvt_pk_f32_bf8((int)w, HI);
@@ -356,6 +375,8 @@ struct VecTile {
   static constexpr int kElemBytes = Kind >= 2 ? 2 : 4;
   static constexpr int kPerVec = 16 / kElemBytes;
   static constexpr uint32_t kRowElems = 64 * kPerVec;
+  template <int P>
+  static constexpr int waves() { return 2; }
 
   // Reduces wavefront `wave`'s rows of the tile: rows k = wave, wave +
   // nwaves, ... of the tile's row set; wavefront 0 also does the
@@ -448,21 +469,22 @@ struct VecTile {
 // number), codes enc(fl(y * fl(1/s))).
 // Tiles start on block boundaries (tile and partition lengths are multiples
 // of 256); only a bucket's last block can be short.
-// One word's four values times the block scale (one multiply each).
-template <class Fmt>
+// One word's four values times the block scale (one multiply each, or one
+// fused with + 0).
+template <class Fmt, bool PLUS0 = false>
 __device__ __forceinline__ void dec4(uint32_t w, float scale, float (&o)[4]) {
   auto lo = Fmt::template dec_pair<false>(w);
   auto hi = Fmt::template dec_pair<true>(w);
-  o[0] = lo[0] * scale;
-  o[1] = lo[1] * scale;
-  o[2] = hi[0] * scale;
-  o[3] = hi[1] * scale;
+  const float v[4] = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    o[j] = PLUS0 ? __builtin_fmaf(v[j], scale, 0.0f) : v[j] * scale;
 }
 
 // Rank-order sum of word k of every rank's codes, plain or Sum2.  dec(word,
 // rank, values) decodes one rank's word.  AGAIN: the rarely taken branch of
-// a caller that has decoded the same words already; the empty asm keeps the
-// compiler from holding those values in registers for it.
+// a caller that has decoded the same words the same way already; the empty
+// asm keeps the compiler from holding those values in registers for it.
 template <bool COMP, bool AGAIN, int P, class Dec>
 __device__ __forceinline__ void sum_word(const uint4 (&raw)[P], int k,
                                          Dec&& dec, float (&y)[4]) {
@@ -485,117 +507,161 @@ __device__ __forceinline__ void sum_word(const uint4 (&raw)[P], int k,
   for (int j = 0; j < 4; ++j) y[j] = acc[j].get();
 }
 
-// Whether the compensated sums of the 8-bit payloads go through binary64
-// (below): from 3 ranks on (64 buckets of e4m3, 2^29 values: 3 ranks 342 ->
-// 314 us, 4 ranks 423 -> 383 us, 16 ranks 1569 -> 1393 us).  At 1 and 2 ranks
-// Sum2 has no addition, or one, to compensate and costs less than the route.
-template <bool COMP, int P>
-constexpr bool kSumF64 = COMP && P >= 3;
-
-// What the binary64 route needs to know of a lane's terms.
-struct TermBound {
-  float t;   // a sum whose nonzero terms are all larger than t in magnitude
-             // is Sum2's exact case (see sum_word_f64)
-  double b;  // how far Sum2's s + c can be from the binary64 sum
-};
-
-// All terms of the lane are at most big = kMax max|s_r| in magnitude.  Where
-// a partial sum of P such terms could overflow, nothing is settled through
-// binary64 (t and b infinite).
+// Sum2's result of value i (0..15) of the lane.
 template <class Fmt, int P>
-__device__ __forceinline__ TermBound term_bound(const float (&s_in)[P]) {
-  // sum_{r=2}^{P-1} r (r + 3) / 2
-  constexpr int kC = ((P - 1) * P * (2 * P - 1) / 6 - 1 +
-                      3 * (P * (P - 1) / 2 - 1)) / 2;
-  float smax = fabsf(s_in[0]);
+__device__ __forceinline__ float sum2_at(const uint4 (&raw)[P],
+                                         const float (&s_in)[P], uint32_t i) {
+  FSum<true, true> acc;
 #pragma unroll
-  for (int r = 1; r < P; ++r) smax = fmaxf(smax, fabsf(s_in[r]));
-  const bool far = !(smax < 0x1p126f / (Fmt::kMax * (float)P));
-  const float big = far ? __builtin_inff() : smax * Fmt::kMax;
-  return {big * ((float)(P * (P + 1) / 2) * 0x1p-24f),
-          (double)big * ((double)(kC + P) * 0x1p-48)};
+  for (int r = 0; r < P; ++r) {
+    const uint32_t lo = __builtin_amdgcn_perm(raw[r].y, raw[r].x, i & 7u);
+    const uint32_t hi = __builtin_amdgcn_perm(raw[r].w, raw[r].z, i & 7u);
+    const float d = Fmt::dec(i < 8u ? lo : hi) * s_in[r];
+    if (r == 0)
+      acc.init(d);
+    else
+      acc.add(d);
+  }
+  return acc.get();
 }
 
-// The Sum2 result of word k's four values, computed through binary64.
+// The compensated row of the 8-bit formats from plain sums, from 3 ranks on
+// (below, Sum2 has at most one addition to compensate).
 //
-// Sum2 in binary32 costs seven dependent operations per rank and value,
-// which made these kernels wait for the VALU and not for memory.  A
-// binary64 running sum D costs two (convert, add), at the same rate, and
-// Sum2's result follows from it.  With u = 2^-24, E the exact sum and m the
-// bound on every |p_r|, Sum2 returns fl32(s + c) where s + sum e_r = E
-// exactly, |e_r| <= u (r + 1) m, and only c's own additions round:
-//   * every nonzero term larger than t = u m P (P + 1) / 2: the terms, so
-//     the e_r and c, are multiples of g >= u min|p_r|, and sum |e_r| < 2^24
-//     g: c is exact, so is D, and the result is D rounded;
-//   * else |s + c - E| <= u^2 m sum_{r=2}^{P-1} r (r + 3) / 2, and D is off
-//     by far less: with b the sum of both, D - b and D + b that round to the
-//     same binary32 value give the result, rounding being monotonic;
-//   * else Sum2 itself, for the word.
-// D's own ties are common (the terms have 24 bits each, so D often needs
-// just one more: 9 % of values), which is why the first test comes first: a
-// term below t appears in 0.2 % of gradient-like values, and one word in 20
-// then needs the third (which tells zero terms from small ones), one in 50
-// the last.  Sum2 never returns -0, which D rounds to only when every term
-// is -0: the second and third test give +0 there.
+// Sum2 in binary32 costs seven dependent operations per rank and value.  But
+// the row's outputs are 8-bit codes and one scale per block, and few of them
+// depend on the correction.  Sum2 returns fl(s + c) with s the plain sum and
+// c the sum of its rounding errors, each at most u |s_r| (u = 2^-24, s_r the
+// partial sums): |c| <= E M with M the largest |s_r| and E = u (P - 1), and a
+// little for c's own rounding.  Every step from s to a code is monotonic, so
+//   * the codes of fl(s - E M) and fl(s + E M), where equal, are the code;
+//   * the scale needs the exact largest magnitude: each lane takes Sum2 of
+//     the largest of its 16 plain sums, and these settle the block's amax if
+//     no lane's second largest can exceed it;
+//   * the values whose two codes differ (about 1 in 30,000 of gradient-like
+//     data) take Sum2 one by one.
+// Returns false where this settles nothing, and the whole row takes Sum2:
+// infinities or NaN, near ties for the largest in one lane, many open codes.
 //
-// Row of 1024 values at 8 ranks without its memory traffic, per SIMD: Sum2
-// 1776 ns, this about 980 ns.  The e4m3 kernel on 128 buckets, 2^30 values
-// in all, 8 ranks: 1.90 -> 1.65 ms (4.6 -> 5.3 TB/s), 5 % above the same
-// kernel with plain sums: what bounds it now is the memory streams.
-template <int P, class Dec>
-__device__ __forceinline__ void sum_word_f64(const uint4 (&raw)[P], int k,
-                                             Dec&& dec, const TermBound& tb,
-                                             float (&y)[4]) {
-  double D[4];
-  float least[4];
+// Where all scales of a lane are powers of two, its sums are multiples of
+// the smallest scale times the format's quantum and often lie halfway between
+// two codes; below 2^24 such multiples they are exact (E = 0).  e5m2 codes
+// span too much for that: such rows take Sum2 at once.
+//
+// Bound: the memory streams, with the arithmetic close behind.  e4m3, 128
+// buckets, 2^30 values, 8 ranks: 1.90 ms with Sum2 for every value, 1.61 ms
+// this way (5.5 TB/s); one message of 2^25 values, 16 ranks, 144 us (binary64
+// sums, which these kernels must not use, 160).  Rows that end in Sum2 pay for
+// both: every value equal, 8 ranks, 80 -> 122 us.  The row's sums are kept for
+// the codes, so registers decide the occupancy: a word at a time, the codes
+// through ld_row (141 -> 124 VGPRs, four wavefronts per SIMD).
+template <class Fmt, int P>
+__device__ __forceinline__ bool row_from_plain(const uint4 (&raw)[P],
+                                               const float (&s_in)[P],
+                                               uint32_t (&w)[4], float& so) {
+  uint32_t mant = 0u;
 #pragma unroll
-  for (int r = 0; r < P; ++r) {
-    float d[4];
-    dec(Word32::get(raw[r], k), r, d);
+  for (int r = 0; r < P; ++r) mant |= __float_as_uint(s_in[r]);
+  const bool pow2 = (mant & 0x7fffffu) == 0u;
+  if constexpr (Fmt::kQuantum < 0x1p-9f) {
+    if (__builtin_expect(__ballot(pow2) != 0, 0)) {
+      uint32_t any = 0u;  // blocks of zeros have equal scales
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      D[j] = r == 0 ? (double)d[j] : D[j] + (double)d[j];
-      least[j] = r == 0 ? fabsf(d[j]) : fminf(least[j], fabsf(d[j]));
+      for (int r = 0; r < P; ++r)
+        any |= (raw[r].x | raw[r].y | raw[r].z | raw[r].w) & 0x7f7f7f7fu;
+      if (__ballot(pow2 && any != 0u) != 0) return false;
     }
   }
-  bool close = false;
+  float y[16], M[16];
+  uint32_t m1 = 0u, m2 = 0u;  // the largest |y|, the index in the low bits,
+                              // and the second largest
+  float mx = 0.0f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    y[j] = (float)D[j];
-    close |= !(least[j] > tb.t);
+  for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int r = 0; r < P; ++r) {
+      float d[4];
+      if (r == 0)
+        // + 0 turns a sum of nothing but -0 into Sum2's +0
+        dec4<Fmt, true>(Word32::get(raw[r], k), s_in[r], d);
+      else
+        dec4<Fmt>(Word32::get(raw[r], k), s_in[r], d);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = 4 * k + j;
+        y[i] = r == 0 ? d[j] : y[i] + d[j];
+        if (r > 0) M[i] = r == 1 ? fabsf(y[i]) : fmaxf(M[i], fabsf(y[i]));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = 4 * k + j;
+      const uint32_t x = (__float_as_uint(y[i]) & 0x7ffffff0u) | (uint32_t)i;
+      m2 = max(min(m1, m2), min(max(m1, m2), x));  // the median
+      m1 = max(m1, x);
+      mx = fmaxf(mx, M[i]);
+    }
+    // one word at a time: the other words' terms would only hold registers
+    __builtin_amdgcn_sched_barrier(0);
   }
-  if (__builtin_expect(__ballot(close) == 0, 1)) return;
-  bool open[4];
-  bool any = false;
+  constexpr float kE = (float)(P - 1) * 0x1.0002p-24f;
+  constexpr float kExact = 0x1p24f * Fmt::kQuantum;
+  float E = kE;
+  if (__ballot(pow2) != 0) {
+    uint32_t least = ~0u;  // the smallest scale's bits, twice, less 1: zeros
+                           // come last
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float lo = (float)(D[j] - tb.b), hi = (float)(D[j] + tb.b);
-    open[j] = !(least[j] > tb.t) && !(lo == hi);
-    if (lo == hi) y[j] = hi;
-    any |= open[j];
+    for (int r = 0; r < P; ++r)
+      least = min(least, (__float_as_uint(s_in[r]) << 1) - 1u);
+    if (pow2 && mx < __uint_as_float((least + 1u) >> 1) * kExact) E = 0.0f;
   }
-  if (__ballot(any) == 0) return;
-  // the smallest nonzero term: twice the magnitude's bits less one, which
-  // puts zero last
-  uint32_t nz[4] = {~0u, ~0u, ~0u, ~0u};
+  float amax = fabsf(sum2_at<Fmt>(raw, s_in, m1 & 15u));
+  amax = fmaxf(amax, __shfl_xor(amax, 8, 16));
+  amax = fmaxf(amax, __shfl_xor(amax, 4, 16));
+  amax = fmaxf(amax, __shfl_xor(amax, 2, 16));
+  amax = fmaxf(amax, __shfl_xor(amax, 1, 16));
+  // below 2^-118 the scale is 1 whatever amax is
+  const float second = __builtin_fmaf(mx, E, __uint_as_float(m2 | 15u));
+  const bool ok = m1 < 0x7f800000u && amax < __builtin_inff() &&
+                  second <= fmaxf(amax, 0x1p-118f);
+  if (__builtin_expect(__ballot(!ok) != 0, 0)) return false;
+  so = amax / Fmt::kMax;
+  if (!(so >= 0x1p-126f)) so = 1.0f;
+  const float inv = 1.0f / so;
+  // |y| * inv is at most kMax and a few of its ulps, so nothing saturates
+  uint32_t open = 0u, lo[4];
 #pragma unroll
-  for (int r = 0; r < P; ++r) {
-    float d[4];
-    uint32_t w = Word32::get(raw[r], k);
-    asm("" : "+v"(w));  // decoded again, not kept (see sum_word)
-    dec(w, r, d);
+  for (int k = 0; k < 4; ++k) {
+    float a[4], b[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      nz[j] = min(nz[j], (__float_as_uint(d[j]) << 1) - 1u);
+    for (int j = 0; j < 4; ++j) {
+      const int i = 4 * k + j;
+      a[j] = __builtin_fmaf(M[i], -E, y[i]) * inv;
+      b[j] = __builtin_fmaf(M[i], E, y[i]) * inv;
+    }
+    lo[k] = Fmt::enc4_small(a[0], a[1], a[2], a[3]);
+    w[k] = Fmt::enc4_small(b[0], b[1], b[2], b[3]);
+    open |= lo[k] ^ w[k];
+    __builtin_amdgcn_sched_barrier(0);
   }
-  any = false;
+  if (__builtin_expect(__ballot(open != 0u) == 0, 1)) return true;
+  uint32_t todo = 0u;  // a bit for each open value
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const bool exact = nz[j] >= __float_as_uint(tb.t) << 1;
-    if (open[j] && exact) y[j] = (float)D[j] + 0.0f;
-    any |= open[j] && !exact;
+  for (int i = 0; i < 16; ++i)
+    if (((lo[i / 4] ^ w[i / 4]) >> (8 * (i % 4)) & 0xffu) != 0u)
+      todo |= 1u << i;
+  if (__ballot(__popc(todo) > 2) != 0) return false;
+  while (__ballot(todo != 0u) != 0) {
+    const uint32_t i = todo ? (uint32_t)__ffs((int)todo) - 1u : 0u;
+    const float v = sum2_at<Fmt>(raw, s_in, i) * inv;
+    const uint32_t code = Fmt::enc4_small(v, 0.0f, 0.0f, 0.0f) & 0xffu;
+    const uint32_t at = 8u * (i & 3u);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+      if (todo && i / 4u == k) w[k] = (w[k] & ~(0xffu << at)) | (code << at);
+    todo &= todo - 1u;
   }
-  if (__ballot(any) != 0) sum_word<true, true>(raw, k, dec, y);
+  return true;
 }
 
 __device__ __forceinline__ uint4 load_codes(const uint8_t* p, uint32_t have) {
@@ -608,6 +674,12 @@ __device__ __forceinline__ uint4 load_codes(const uint8_t* p, uint32_t have) {
 template <bool COMP, class Fmt>
 struct Fp8Tile {
   static constexpr uint32_t kRowElems = 1024;  // 64 lanes x 16 codes
+  // Wavefronts per SIMD that the registers are kept to (more spill): the
+  // loads of others hide behind a row's arithmetic.
+  template <int P>
+  static constexpr int waves() {
+    return COMP && P >= 3 ? (P <= 8 ? 4 : 3) : 2;
+  }
 
   // Row q: lane l owns codes el .. el + 16 of block blk.  FULL: the
   // whole row is inside the bucket (every lane has 16 codes), which spares
@@ -624,8 +696,7 @@ struct Fp8Tile {
 #pragma unroll
     for (int r = 0; r < P; ++r) {
       if (FULL) {
-        raw[r] = ld_stream(reinterpret_cast<const uint4*>(
-                               in[r] + (size_t)q * kRowElems) + lane_id());
+        raw[r] = ld_row(in[r] + (size_t)q * kRowElems, lane_id());
         s_in[r] = sc[r][blk];
       } else {
         raw[r] = have ? load_codes(in[r] + el, have) : make_uint4(0, 0, 0, 0);
@@ -638,55 +709,38 @@ struct Fp8Tile {
     const auto dec = [&](uint32_t w, int r, float(&d)[4]) {
       dec4<Fmt>(w, s_in[r], d);
     };
-    float y[16];
-    float amax = 0.0f;
-    const auto keep = [&](int k, const float(&v)[4]) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        y[4 * k + j] = v[j];
-        if (FULL || (uint32_t)(4 * k + j) < have)
-          amax = fmaxf(amax, fabsf(v[j]));
-      }
-    };
-    if constexpr (kSumF64<COMP, P>) {
-      const TermBound tb = term_bound<Fmt>(s_in);
+    uint32_t w[4];
+    float so;
+    bool done = false;
+    if constexpr (COMP && P >= 3 && FULL)
+      done = row_from_plain<Fmt>(raw, s_in, w, so);
+    if (!done) {
+      float y[16];
+      float amax = 0.0f;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float v[4];
-        sum_word_f64(raw, k, dec, tb, v);
-        keep(k, v);
-      }
-      // infinite codes (e5m2): what Sum2 makes of them
-      if (__builtin_expect(__ballot(amax == __builtin_inff()) != 0, 0)) {
-        amax = 0.0f;
+        sum_word<COMP, COMP && P >= 3 && FULL>(raw, k, dec, v);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          float v[4];
-          sum_word<true, true>(raw, k, dec, v);
-          keep(k, v);
+        for (int j = 0; j < 4; ++j) {
+          y[4 * k + j] = v[j];
+          if (FULL || (uint32_t)(4 * k + j) < have)
+            amax = fmaxf(amax, fabsf(v[j]));
         }
       }
-    } else {
+      // max over the 16 lanes of the block
+      amax = fmaxf(amax, __shfl_xor(amax, 8, 16));
+      amax = fmaxf(amax, __shfl_xor(amax, 4, 16));
+      amax = fmaxf(amax, __shfl_xor(amax, 2, 16));
+      amax = fmaxf(amax, __shfl_xor(amax, 1, 16));
+      so = amax / Fmt::kMax;
+      if (!(so >= 0x1p-126f)) so = 1.0f;
+      const float inv = 1.0f / so;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float v[4];
-        sum_word<COMP, false>(raw, k, dec, v);
-        keep(k, v);
-      }
+      for (int k = 0; k < 4; ++k)
+        w[k] = Fmt::enc4(y[4 * k] * inv, y[4 * k + 1] * inv,
+                         y[4 * k + 2] * inv, y[4 * k + 3] * inv);
     }
-    // max over the 16 lanes of the block
-    amax = fmaxf(amax, __shfl_xor(amax, 8, 16));
-    amax = fmaxf(amax, __shfl_xor(amax, 4, 16));
-    amax = fmaxf(amax, __shfl_xor(amax, 2, 16));
-    amax = fmaxf(amax, __shfl_xor(amax, 1, 16));
-    float so = amax / Fmt::kMax;
-    if (!(so >= 0x1p-126f)) so = 1.0f;
-    const float inv = 1.0f / so;
-    uint32_t w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      w[k] = Fmt::enc4(y[4 * k] * inv, y[4 * k + 1] * inv, y[4 * k + 2] * inv,
-                       y[4 * k + 3] * inv);
     if (FULL || have == 16u) {
       st_row(out + (size_t)q * kRowElems, lane_id(),
              make_uint4(w[0], w[1], w[2], w[3]));
@@ -771,16 +825,22 @@ __device__ __forceinline__ void mx_dec4(uint32_t w, float scale,
   o[3] = hi[1];
 }
 
-// Whether the exact sum, rounded once, is what Sum2 returns for a lane's
-// values (32 buckets, 2^28 values, 8 ranks: 0.606 -> 0.509 ms, 4.9 -> 5.9
-// TB/s, the time of plain sums; a row body 1540 -> 630 ns per SIMD): every decoded term is a multiple of g = 2^-9 2^(bmin - 127) of at
-// most 448 * 2^(bmax - 127), so for bmax - bmin <= 23 and up to 16 ranks
-// Sum2's errors add up to at most 135 u 448 2^(bmax - 127) <= 2^24 g: its
-// correction is exact and its result the exact sum rounded; and the
-// binary64 sum is exact too (22 + 23 bits).  Above byte 240 a partial sum
-// could leave binary32's range.
-__device__ __forceinline__ bool mx_exact(uint32_t bmin, uint32_t bmax) {
-  return bmax <= 240u && bmax - bmin <= 23u;
+// Terms of at most 448, counted in their smallest scale's quantum 2^-9, add up
+// below 2^31 if the ranks' scales, relative to the smallest, add up to this at
+// most; so do P ranks' with scale bytes mx_spread(P) apart.
+constexpr uint32_t kMxUnits = ((1u << 31) - 1u) / (448u * 512u);
+constexpr uint32_t mx_spread(int P) {
+  uint32_t d = 0;
+  while (((uint32_t)P << (d + 1)) <= kMxUnits) ++d;
+  return d;
+}
+
+// Whether any byte of w is a NaN code, in bit 7 of each byte, or-ed to acc:
+// adding 1 to a byte changes its sign bit only if the other bits are set (a
+// carry out of a byte comes from a NaN there).
+__device__ __forceinline__ uint32_t mx_nan(uint32_t acc, uint32_t w) {
+  return __builtin_amdgcn_bitop3_b32(acc, w + 0x01010101u, w,
+                                     0xf0 | (0xcc ^ 0xaa));
 }
 
 // Codes of y[0..16) / 2^(b - 127), four per word (code j in byte j).
@@ -821,6 +881,8 @@ __device__ __forceinline__ float pair_max(float v) {
 template <bool COMP>
 struct MxTile {
   static constexpr uint32_t kRowElems = 1024;  // 64 lanes x 16 codes
+  template <int P>
+  static constexpr int waves() { return 2; }
 
   template <int P, bool FULL>
   __device__ __forceinline__ static void row(const uint8_t* const (&in)[P],
@@ -843,62 +905,93 @@ struct MxTile {
       }
     }
     if (FULL) __builtin_amdgcn_sched_barrier(0);
+    uint32_t base = 0u;  // of the scale bytes in b_in
     const auto dec = [&](uint32_t w, int r, float(&d)[4]) {
-      mx_dec4(w, e8m0_operand(b_in[r]), d);
+      mx_dec4(w, e8m0_operand(b_in[r] + base), d);
     };
-    bool sum2 = COMP;  // the binary32 Sum2 itself
-    if constexpr (kSumF64<COMP, P>) {
-      uint32_t bmin = b_in[0], bmax = b_in[0];
+    float y[16];
+    float amax = 0.0f;
+    // From 3 ranks on the compensated sum goes through integers.  Every term
+    // is a multiple of g = 2^-9 2^(bmin - 127), of 4 significant bits and at
+    // most 448 * 2^(bmax - 127), so for bmax - bmin <= 23 and up to 16 ranks
+    // Sum2's errors add up to at most 135 u 448 2^(bmax - 127) <= 2^24 g: its
+    // correction is exact and its result the exact sum rounded once; and for
+    // scales close enough (8 ranks: 2^10) the sum in units of g fits 32 bits.
+    // Above byte 240 a partial sum could leave binary32's range.  Other rows,
+    // and those with NaN codes, take Sum2.  32 buckets, 2^28 values, 8 ranks:
+    // 0.61 ms with Sum2, 0.53 this way (5.7 TB/s); scales 2^20 apart, 2^25
+    // values, 89 against 77 us.
+    bool sum2 = COMP;
+    if constexpr (COMP && P >= 3) {
+      uint32_t bmin = b_in[0], bmax = b_in[0], nan = 0u;
 #pragma unroll
       for (int r = 1; r < P; ++r) {
         bmin = min(bmin, b_in[r]);
         bmax = max(bmax, b_in[r]);
       }
-      bool exact = mx_exact(bmin, bmax);
+#pragma unroll
+      for (int r = 0; r < P; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) nan = mx_nan(nan, Word32::get(raw[r], k));
+      bool exact = bmax <= 240u && bmax - bmin <= mx_spread(P);
       if (__ballot(!exact) != 0) {
         // all-zero blocks carry byte 0: their scale does not count
+        const uint32_t none = 256u;
         bmin = 255u;
         bmax = 0u;
 #pragma unroll
         for (int r = 0; r < P; ++r) {
           const bool zero = ((raw[r].x | raw[r].y | raw[r].z | raw[r].w) &
-                             0x7f7f7f7fu) == 0u;
-          bmin = min(bmin, zero ? 255u : b_in[r]);
+                             0x7f7f7f7fu) == 0u && b_in[r] != 255u;
+          if (zero) b_in[r] = none;
+          bmin = min(bmin, b_in[r]);
           bmax = max(bmax, zero ? 0u : b_in[r]);
         }
-        exact = bmin == 255u && bmax == 0u ? true : mx_exact(bmin, bmax);
-      }
-      sum2 = __ballot(!exact) != 0;
-    }
-    float y[16];
-    float amax = 0.0f;
-    if (kSumF64<COMP, P> && !sum2) {
-      // binary64 running sums (exact here), rounded once; + 0 turns -0 into
-      // Sum2's +0
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        double D[4];
+        if (bmin > bmax) bmin = bmax = 127u;
+        // and the other ranks may lie further apart the fewer are far up
+        uint32_t sum = 0u;
 #pragma unroll
         for (int r = 0; r < P; ++r) {
-          float d[4];
-          dec(Word32::get(raw[r], k), r, d);
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            D[j] = r == 0 ? (double)d[j] : D[j] + (double)d[j];
+          if (b_in[r] == none) b_in[r] = bmin;
+          sum += 1u << min(b_in[r] - bmin, 14u);
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[4 * k + j] = (float)D[j] + 0.0f;
-        // one word at a time: the other words' terms would only hold
-        // registers
-        __builtin_amdgcn_sched_barrier(0);
+        exact = bmax <= 240u && sum <= kMxUnits;
       }
-    } else {
+      // from here on relative to the smallest, times 2^9
+      base = bmin - 136u;
+#pragma unroll
+      for (int r = 0; r < P; ++r) b_in[r] -= base;
+      sum2 = __ballot(!exact || (nan & 0x80808080u) != 0u) != 0;
+      if (!sum2) {
+        // 2^(bmin - 136), which may be subnormal
+        const float unit = __builtin_ldexpf(1.0f, (int)bmin - 136);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          int n[4];
+#pragma unroll
+          for (int r = 0; r < P; ++r) {
+            float d[4];
+            mx_dec4(Word32::get(raw[r], k), e8m0_operand(b_in[r]), d);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              n[j] = r == 0 ? (int)d[j] : n[j] + (int)d[j];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[4 * k + j] = (float)n[j] * unit;
+          // one word at a time: the other words' terms would only hold
+          // registers
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if (!(COMP && P >= 3) || sum2) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float v[4];
-        sum_word<COMP, kSumF64<COMP, P>>(raw, k, dec, v);
+        sum_word<COMP, false>(raw, k, dec, v);
 #pragma unroll
         for (int j = 0; j < 4; ++j) y[4 * k + j] = v[j];
+        if (COMP) __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
