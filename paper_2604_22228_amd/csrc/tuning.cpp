@@ -125,11 +125,24 @@ TuneChoice tune_lookup(const std::vector<TuneRow>& rows, int dtype, int op,
 // fp32, 8 ranks, 2^18 elements, 8 / 16 / 32 rows 17.1 / 16.2 / 19.0 us; e4m3,
 // 8 ranks, 2^20, 4 / 8 / 16 / 32 rows 21.9 / 20.3 / 22.5 / 28.2 us.
 //
-// One group of 8 wavefronts per compute unit (fp32 8 ranks 2^24: 106 against
-// 117 us with two), two where arithmetic must hide behind the loads of
-// others (8-bit: e4m3 2 ranks 2^28 174 against 217 us).  Rows in flight per
-// lane: as many as a wavefront has in a tile, at most 2 from 5 ranks on (6
-// ranks 2^26: 304 against 307 us).
+// At 7 and 8 ranks a message of more than 256 and at most 512 tiles of 16 rows
+// gets tiles of 32, one for each workgroup of the 256 compute units instead of
+// two for some: a second tile costs its claim and a latency.  Kernel us at 16
+// / 32 rows: fp32, 8 ranks, 4500 rows 18.1 / 17.4, 6000 20.0 / 19.0, 8192 23.1
+// / 21.9, 9000 24.6 / 26.2; bf16 8192 23.2 / 22.6, bf16 pair 27.4 / 25.8.  (At
+// 16 ranks fp32 6000 29.0 / 28.3 but 8192 33.6 / 34.2, bf16 37.4 / 38.9.)
+//
+// One group of 8 wavefronts per compute unit at every size (kernel us with one
+// / two, fp32, 8 ranks: 2^20 elements 16.2 / 16.3, 2^21 22.4 / 25.0, 2^22 33.9
+// / 38.8, 2^24 99 / 111; two of 4 wavefronts as two of 8), two where arithmetic
+// must hide behind the loads of others (8-bit: e4m3 2 ranks 2^28 174 against
+// 217 us, 8 ranks 2^26 138 / 126, 9 ranks 154 / 140).  From 10 ranks on (MX
+// blocks: 9) the registers allow three wavefronts per SIMD or two, and the
+// launch's residency cap leaves one group; three groups of 4 wavefronts in its
+// place are slower, but for e4m3 at 10 to 13 ranks and 2^26 with tiles of half
+// the rows (one of 8 / three of 4: 12 ranks 2^24 57 / 77 us, 2^26 192 / 181; MX
+// 160 / 175).  Rows in flight per lane: as many as a wavefront has in a tile, at
+// most 2 from 5 ranks on (6 ranks 2^26: 304 against 307 us).
 TuneChoice shape_rule(int dtype, int ranks, uint64_t bytes_per_rank) {
   const bool bits8 = dtype >= 3 && dtype <= 5;
   const uint64_t rows = (bytes_per_rank + 1023) / 1024;
@@ -138,6 +151,8 @@ TuneChoice shape_rule(int dtype, int ranks, uint64_t bytes_per_rank) {
     tile = ranks <= 6 || rows <= 16384 ? 32 : 16;
   else
     tile = ranks <= 2 ? 64 : (ranks <= 6 ? 32 : 16);
+  if (!bits8 && tile == 16 && ranks <= 8 && rows > 4096 && rows <= 8192)
+    tile = 32;
   uint64_t fit = rows / (bits8 ? 128 : 64) / 8 * 8;
   if (fit < 8) fit = 8;
   if (tile > fit) tile = fit;
