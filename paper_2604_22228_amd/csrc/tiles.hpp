@@ -507,6 +507,22 @@ __device__ __forceinline__ void sum_word(const uint4 (&raw)[P], int k,
   for (int j = 0; j < 4; ++j) y[j] = acc[j].get();
 }
 
+// Max over the 16 lanes of a block: rotations within a DPP row (through LDS
+// shuffles each step waits for a round trip: direct kernel, e4m3, 3 ranks, 2^26
+// values, 70 against 66 us).
+__device__ __forceinline__ float row16_max(float v) {
+  const auto step = [&](auto ctrl) {
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(
+                     __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf,
+                     false)));
+  };
+  step(std::integral_constant<int, 0x128>{});  // row_ror:8
+  step(std::integral_constant<int, 0x124>{});
+  step(std::integral_constant<int, 0x122>{});
+  step(std::integral_constant<int, 0x121>{});
+  return v;
+}
+
 // Sum2's result of value i (0..15) of the lane.
 template <class Fmt, int P>
 __device__ __forceinline__ float sum2_at(const uint4 (&raw)[P],
@@ -551,8 +567,9 @@ __device__ __forceinline__ float sum2_at(const uint4 (&raw)[P],
 // Bound: the memory streams, with the arithmetic close behind.  e4m3, 128
 // buckets, 2^30 values, 8 ranks: 1.90 ms with Sum2 for every value, 1.61 ms
 // this way (5.5 TB/s); one message of 2^25 values, 16 ranks, 144 us (binary64
-// sums, which these kernels must not use, 160).  Rows that end in Sum2 pay for
-// both: every value equal, 8 ranks, 80 -> 122 us.  The row's sums are kept for
+// sums, which these kernels must not use, 160).  With 3 ranks it costs what
+// Sum2 does (2^26 values, direct kernel 66 / 68 us), with 4 less (76 / 84).
+// Rows that end in Sum2 pay for both: every value equal, 8 ranks, 80 -> 122 us.  The row's sums are kept for
 // the codes, so registers decide the occupancy: a word at a time, the codes
 // through ld_row (141 -> 124 VGPRs, four wavefronts per SIMD).
 template <class Fmt, int P>
@@ -615,11 +632,7 @@ __device__ __forceinline__ bool row_from_plain(const uint4 (&raw)[P],
       least = min(least, (__float_as_uint(s_in[r]) << 1) - 1u);
     if (pow2 && mx < __uint_as_float((least + 1u) >> 1) * kExact) E = 0.0f;
   }
-  float amax = fabsf(sum2_at<Fmt>(raw, s_in, m1 & 15u));
-  amax = fmaxf(amax, __shfl_xor(amax, 8, 16));
-  amax = fmaxf(amax, __shfl_xor(amax, 4, 16));
-  amax = fmaxf(amax, __shfl_xor(amax, 2, 16));
-  amax = fmaxf(amax, __shfl_xor(amax, 1, 16));
+  const float amax = row16_max(fabsf(sum2_at<Fmt>(raw, s_in, m1 & 15u)));
   // below 2^-118 the scale is 1 whatever amax is
   const float second = __builtin_fmaf(mx, E, __uint_as_float(m2 | 15u));
   const bool ok = m1 < 0x7f800000u && amax < __builtin_inff() &&
@@ -728,11 +741,7 @@ struct Fp8Tile {
             amax = fmaxf(amax, fabsf(v[j]));
         }
       }
-      // max over the 16 lanes of the block
-      amax = fmaxf(amax, __shfl_xor(amax, 8, 16));
-      amax = fmaxf(amax, __shfl_xor(amax, 4, 16));
-      amax = fmaxf(amax, __shfl_xor(amax, 2, 16));
-      amax = fmaxf(amax, __shfl_xor(amax, 1, 16));
+      amax = row16_max(amax);
       so = amax / Fmt::kMax;
       if (!(so >= 0x1p-126f)) so = 1.0f;
       const float inv = 1.0f / so;
