@@ -216,7 +216,8 @@ def tune(keys, grid, warmup, reps, log=print):
 
 
 def read_table(path):
-    """The rows of an existing table, in the form tune() returns them, so that a partial run can keep the other keys."""
+    """The rows of an existing table, in the form tune() returns them, so
+    that a partial run can keep the other keys."""
     rows = []
     with open(path) as f:
         for line in f:
@@ -241,7 +242,8 @@ def write_table(rows, path):
     lines = ["# Tuned launch parameters of libpcoll on MI355X (gfx950), "
              "written by paper_2604_22228_amd/autotune.py.",
              "# dtype op ranks graph log2_lo log2_hi tile_elems "
-             "groups_per_cu interleave waves batch unroll   # median kernel ms"]
+             "groups_per_cu interleave waves batch unroll   # median ms of "
+             "an epoch between events"]
     # graph rows first: the first matching row wins, and a direct row
     # ("*") also serves graph replays
     keys = sorted(groups, key=lambda k: 0 if k[3] == "1" else 1)
