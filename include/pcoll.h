@@ -417,8 +417,13 @@ int pcoll_set_config(pcoll_req_t req, const pcoll_config_t *cfg);
  * nparts, nranks) and pcoll_bind for one bucket (rank_bufs: nranks device
  * pointers; out; rank_scales / out_scale for the 8-bit floats, the lo
  * array as out_scale for bf16 pairs); compensation and rows in flight are
- * the tuned defaults (and the PCOLL_COMP, PCOLL_UNROLL environment), the
- * launch shape its own.  PCOLL_ERR_UNSUPPORTED for more than
+ * the tuned defaults (and the PCOLL_COMP, PCOLL_UNROLL environment).  The
+ * launch shape is the kernel's own rule -- the table's rows, also those of a
+ * PCOLL_TUNE_FILE, are shapes of the persistent kernel -- unless the
+ * environment gives one: PCOLL_TILE (elements per workgroup),
+ * PCOLL_INTERLEAVE, PCOLL_GROUP_WAVES, and PCOLL_GROUPS or
+ * PCOLL_GROUPS_PER_CU (the most workgroups; values out of range are
+ * ignored).  PCOLL_ERR_UNSUPPORTED for more than
  * PCOLL_NOALLOC_MAX_PARTS partitions; other errors as pcoll_init and
  * pcoll_bind.  The first call reads the tuned table (once per process). */
 int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype, pcoll_op_t op,

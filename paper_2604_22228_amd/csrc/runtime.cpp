@@ -432,6 +432,14 @@ int apply_config(pcoll_req_t r, const pcoll_config_t& c) {
   return PCOLL_SUCCESS;
 }
 
+// Whether sums are compensated by default: on for the 8-bit floats, bf16
+// pairs and 16 ranks or more, PCOLL_COMP overrides.
+bool compensated(int dtype, int op, int nranks) {
+  if (op != PCOLL_SUM || dtype == PCOLL_INT32) return false;
+  return env_int("PCOLL_COMP", is_fp8(dtype) || dtype == PCOLL_BF16_PAIR ||
+                                   nranks >= 16) != 0;
+}
+
 // The default configuration of a request of `bytes` per rank: the tuned
 // table's row, then the environment overrides.
 pcoll_config_t config_for(int dtype, int op, int nranks, uint64_t bytes) {
@@ -451,13 +459,7 @@ pcoll_config_t config_for(int dtype, int op, int nranks, uint64_t bytes) {
   c.publish_batch = env_int("PCOLL_PUBLISH_BATCH", t.publish_batch);
   c.groups = env_int("PCOLL_GROUPS", 0);
   c.groups_per_cu = env_int("PCOLL_GROUPS_PER_CU", t.groups_per_cu);
-  const bool float_sum = op == PCOLL_SUM && dtype != PCOLL_INT32;
-  // compensated accumulation: on for the 8-bit floats, bf16 pairs and 16
-  // ranks or more
-  int comp = float_sum && (is_fp8(dtype) || dtype == PCOLL_BF16_PAIR ||
-                           nranks >= 16);
-  comp = env_int("PCOLL_COMP", comp);
-  c.comp = float_sum && comp ? 1 : 0;
+  c.comp = compensated(dtype, op, nranks) ? 1 : 0;
   c.timeout_ms = env_int("PCOLL_TIMEOUT_MS", 10000);
   c.debug = env_int("PCOLL_DEBUG", 0) & 7;
   c.producers = env_int("PCOLL_PRODUCERS", -1);
@@ -472,38 +474,35 @@ pcoll_config_t default_config(const pcoll_req_s* r) {
 }
 
 
-// Launch shape of the direct kernel: workgroups of 4 wavefronts, a row each
-// per wavefront, two for 4-byte elements once the message has 4096 rows (512
-// tiles, two per compute unit).  Small tiles spread a small message over the
-// whole chip and keep its parallel streams close together; the hardware hands
-// out the next one at no cost.  Measured at 8 ranks, 4 / 8 rows per tile: fp32
-// 4 MiB per rank 8.8 / 8.0 us, 256 MiB 397 / 395 us; bf16 2 MiB 6.7 / 6.8 us,
-// 128 MiB 189 / 196 us; e4m3 2^24 elements 32.3 / 32.6 us.  (The persistent
-// kernel's tiles, 32 rows by 8 wavefronts: 9.7, 406, 8.4, 205, 32.2 us.)  Bands
-// of 8 tiles: up to 2 % over consecutive rows from 64 MiB per rank on, no
-// difference below.
-//
-// Large messages of many streams run best with two of these workgroups per
-// compute unit, not the four that the registers allow: fewer places of each
-// buffer are open in memory at once.  Reserving LDS that nothing uses keeps it
-// at two; then 8 rows per tile and bands of 16.  Four / two workgroups: fp32,
-// 8 ranks, 256 MiB each 398 / 364 us (6.6 TB/s), 64 MiB 102 / 97 us, 4 ranks
-// 128 MiB 112 / 103 us; 12 ranks 128 MiB 297 / 266 us; bf16, 8 ranks, 32 MiB
-// 55 / 51 us; int32, 16 ranks, 16 MiB 55 / 52 us.  No gain below 128 MiB of
-// inputs (fp32, 8 ranks, 16 MiB: 27.6 / 27.7 us), a loss with fewer streams
-// (fp32, 1 rank, 128 MiB: 44 / 56 us) and for the 8-bit types, which need the
-// wavefronts for their arithmetic (e4m3 110 / 135 us).
-constexpr int kDirectWaves = 4;
-struct DirectShape {
-  uint32_t rows;  // per tile
-  uint32_t band;
-  unsigned lds;
+// The allocation-free epoch's settings: compensation and rows in flight as
+// the request path takes them, and the launch shape the environment asks for
+// (tile, workgroups, layout, wavefronts; the workgroups of a persistent
+// launch are the most a direct one may have).
+struct DirectConfig {
+  bool comp, deep;
+  DirectOverride shape;
 };
-DirectShape direct_shape(int dtype, int nranks, uint64_t count, uint64_t rows) {
-  const uint64_t bytes = count * (uint64_t)elem_bytes(dtype) * (uint64_t)nranks;
-  if (!is_fp8(dtype) && nranks >= 4 && bytes >= (1ull << 27))
-    return {8u, 16u, 64000u};
-  return {elem_bytes(dtype) == 4 && rows >= 4096u ? 8u : 4u, 8u, 0u};
+int direct_config(int dtype, int op, int nranks, uint64_t bytes,
+                  DirectConfig* out) {
+  const int graph = env_int("PCOLL_GRAPH", 0) ? 1 : 0;
+  TuneChoice t = tune_lookup(tune_rows(), dtype, op, nranks, graph, bytes);
+  if (!t.matched) t = shape_rule(dtype, nranks, bytes);
+  out->comp = compensated(dtype, op, nranks);
+  out->deep = env_int("PCOLL_UNROLL", t.unroll) != 2;
+  DirectOverride& o = out->shape;
+  o.tile_elems = env_int("PCOLL_TILE", 0);
+  o.interleave = env_int("PCOLL_INTERLEAVE", -1);
+  o.group_waves = env_int("PCOLL_GROUP_WAVES", 0);
+  o.groups = env_int("PCOLL_GROUPS", 0);
+  const int per_cu = env_int("PCOLL_GROUPS_PER_CU", 0);
+  if (o.groups <= 0 && per_cu > 0) {
+    int dev = 0, cus = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount,
+                                  dev));
+    o.groups = std::min(per_cu, 64) * cus;
+  }
+  return PCOLL_SUCCESS;
 }
 
 void destroy(pcoll_req_t r) {
@@ -1319,9 +1318,10 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
     return PCOLL_ERR_ARG;
   }
   if (count == 0) return PCOLL_SUCCESS;
-  const pcoll_config_t c = config_for(
-      dtype, op, nranks, (uint64_t)count * (uint64_t)elem_bytes(dtype));
-  const uint64_t re = row_elems(dtype);
+  DirectConfig c{};
+  if (const int rc = direct_config(dtype, op, nranks,
+                                   count * (uint64_t)elem_bytes(dtype), &c))
+    return rc;
   DirectArgs a{};
   for (int q = 0; q < nranks; ++q) {
     a.bucket.in[q] = rank_bufs[q];
@@ -1335,25 +1335,16 @@ int pcoll_reduce_noalloc(size_t count, pcoll_dtype_t dtype_, pcoll_op_t op_,
   // (the operation is elementwise, scale blocks count from the message's
   // start): one span, unless 32-bit row numbers ask for the partitions
   a.span = count <= (1ull << 31) ? (uint64_t)count : ps;
-  const uint64_t spans = (count + a.span - 1) / a.span;
-  const uint64_t span_rows = (a.span + re - 1) / re;
-  const uint64_t total_rows = (count + re - 1) / re;
-  const DirectShape shape = direct_shape(dtype, nranks, count, total_rows);
-  a.tile_rows = shape.rows;
-  uint64_t groups;
-  for (;; a.tile_rows *= 2u) {
-    a.span_tiles = (uint32_t)((span_rows + a.tile_rows - 1) / a.tile_rows);
-    groups = spans * a.span_tiles;
-    // a grid has fewer than 2^32 threads: larger tiles for what would need
-    // more (64 GiB a rank in bf16 and the 8-bit types, 128 GiB in 4-byte
-    // ones); one tile a span always fits
-    if (groups * (64u * kDirectWaves) < (1ull << 32)) break;
-  }
-  a.row_shift = (uint32_t)__builtin_ctzll(re);
+  const DirectShape shape =
+      direct_shape(dtype, nranks, count, a.span, c.shape);
+  a.span_tiles = shape.span_tiles;
+  a.tile_rows = shape.tile_rows;
+  a.row_shift = (uint32_t)__builtin_ctzll(row_elems(dtype));
   a.interleave = shape.band;
-  const Launch l{(int)groups, kDirectWaves, static_cast<hipStream_t>(stream),
+  const Launch l{(int)shape.groups, shape.waves,
+                 static_cast<hipStream_t>(stream),
                  nullptr, nullptr, nullptr, shape.lds};
-  HIP_TRY(launch_reduce(a, dtype, op, c.comp != 0, c.unroll != 2, nranks, l));
+  HIP_TRY(launch_reduce(a, dtype, op, c.comp, c.deep, nranks, l));
   return PCOLL_SUCCESS;
 }
 

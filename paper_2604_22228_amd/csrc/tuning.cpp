@@ -1,6 +1,7 @@
 // Tuned-table parsing and lookup (see tuning.hpp).
 #include "tuning.hpp"
 
+#include <algorithm>
 #include <sstream>
 
 namespace pcoll {
@@ -159,6 +160,73 @@ TuneChoice shape_rule(int dtype, int ranks, uint64_t bytes_per_rank) {
   const int row_elems = bits8 ? 1024 : (dtype == 2 || dtype == 6 ? 512 : 256);
   return {(int)tile * row_elems, bits8 ? 2 : 1, bits8 ? 0 : 8, 8, 64,
           ranks >= 5 && ranks <= 8 ? 2 : 4, false};
+}
+
+// Launch shape of the direct kernel: workgroups of 4 wavefronts, a row each
+// per wavefront, two for 4-byte elements once the message has 4096 rows (512
+// tiles, two per compute unit).  Small tiles spread a small message over the
+// whole chip and keep its parallel streams close together; the hardware hands
+// out the next one at no cost.  Measured at 8 ranks, 4 / 8 rows per tile: fp32
+// 4 MiB per rank 8.8 / 8.0 us, 256 MiB 397 / 395 us; bf16 2 MiB 6.7 / 6.8 us,
+// 128 MiB 189 / 196 us; e4m3 2^24 elements 32.3 / 32.6 us.  (The persistent
+// kernel's tiles, 32 rows by 8 wavefronts: 9.7, 406, 8.4, 205, 32.2 us.)  Bands
+// of 8 tiles: up to 2 % over consecutive rows from 64 MiB per rank on, no
+// difference below.
+//
+// Large messages of many streams run best with two of these workgroups per
+// compute unit, not the three to eight that the registers allow (bf16 and
+// compensated sums to plain fp32 and int32): fewer places of each buffer are
+// open in memory at once.  Reserving LDS that nothing uses keeps it at two;
+// then 8 rows per tile and bands of 16.  Unreserved / two workgroups: fp32,
+// 8 ranks, 256 MiB each 398 / 364 us (6.6 TB/s), 64 MiB 102 / 97 us, 4 ranks
+// 128 MiB 112 / 103 us; 12 ranks 128 MiB 297 / 266 us; bf16, 8 ranks, 32 MiB
+// 55 / 51 us; int32, 16 ranks, 16 MiB 55 / 52 us.  No gain below 128 MiB of
+// inputs (fp32, 8 ranks, 16 MiB: 27.6 / 27.7 us), a loss with fewer streams
+// (fp32, 1 rank, 128 MiB: 44 / 56 us) and for the 8-bit types, which need the
+// wavefronts for their arithmetic (e4m3 110 / 135 us).
+DirectShape direct_shape(int dtype, int ranks, uint64_t count, uint64_t span,
+                         const DirectOverride& o) {
+  const bool bits8 = dtype >= 3 && dtype <= 5;
+  const uint64_t elem = bits8 ? 1 : (dtype == 2 || dtype == 6 ? 2 : 4);
+  const uint64_t row_elems = 1024 / elem;
+  const uint64_t rows = (count + row_elems - 1) / row_elems;
+  const uint64_t spans = (count + span - 1) / span;
+  const uint64_t span_rows = (span + row_elems - 1) / row_elems;
+  DirectShape s{};
+  s.waves = 4;
+  if (!bits8 && ranks >= 4 && count * elem * (uint64_t)ranks >= (1ull << 27)) {
+    s.tile_rows = 8;
+    s.band = 16;
+    s.lds = 64000;
+  } else {
+    s.tile_rows = elem == 4 && rows >= 4096 ? 8 : 4;
+    s.band = 8;
+  }
+  // a shape of the caller's own takes no reserved LDS: how many of its
+  // workgroups fit is the caller's choice too
+  const bool waves = o.group_waves >= 1 && o.group_waves <= 8;
+  if (waves) s.waves = o.group_waves;
+  if (o.tile_elems > 0)
+    s.tile_rows = (uint32_t)std::max<uint64_t>(
+        1, (uint64_t)o.tile_elems / row_elems);
+  if (o.groups > 0)
+    s.tile_rows = (uint32_t)std::min(
+        span_rows, std::max<uint64_t>(s.tile_rows,
+                                      (rows + (uint64_t)o.groups - 1) /
+                                          (uint64_t)o.groups));
+  if (waves || o.tile_elems > 0 || o.groups > 0) s.lds = 0;
+  for (;; s.tile_rows *= 2u) {
+    s.span_tiles = (uint32_t)((span_rows + s.tile_rows - 1) / s.tile_rows);
+    s.groups = spans * s.span_tiles;
+    // a grid has fewer than 2^32 threads: larger tiles for what would need
+    // more (64 GiB a rank in bf16 and the 8-bit types, 128 GiB in 4-byte
+    // ones); one tile a span always fits
+    if (s.groups * (64ull * (uint64_t)s.waves) < (1ull << 32)) break;
+  }
+  if (o.interleave >= 0 && o.interleave <= (1 << 20))
+    s.band = o.interleave == 1 ? (uint32_t)std::min<uint64_t>(s.groups, 1u << 20)
+                               : (uint32_t)o.interleave;
+  return s;
 }
 
 }  // namespace pcoll

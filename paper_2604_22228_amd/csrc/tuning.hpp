@@ -44,12 +44,34 @@ struct TuneChoice {
 // Parses a table; malformed lines are skipped.  Returns the rows.
 std::vector<TuneRow> parse_tune_table(const std::string& text);
 
-// First matching row, or the built-in default.
+// First matching row, or (matched = false) a plain default, in whose place the
+// runtime takes shape_rule.
 TuneChoice tune_lookup(const std::vector<TuneRow>& rows, int dtype, int op,
                        int ranks, int graph, uint64_t bytes_per_rank);
 
 // The launch shape where the table has no row: from the payload type, the
 // ranks and the size alone.
 TuneChoice shape_rule(int dtype, int ranks, uint64_t bytes_per_rank);
+
+// Launch shape of the direct kernel: `groups` workgroups of `waves`
+// wavefronts, one for each of the span_tiles tiles of tile_rows rows of every
+// span; `band` the tile layout, `lds` reserved per workgroup and never used.
+struct DirectShape {
+  uint32_t tile_rows;
+  uint32_t span_tiles;
+  uint64_t groups;
+  uint32_t band;
+  int waves;
+  unsigned lds;
+};
+// What a caller's environment sets of it; values out of range count as unset.
+struct DirectOverride {
+  int tile_elems = 0;   // > 0: elements per tile
+  int groups = 0;       // > 0: no more workgroups than this (one per span)
+  int interleave = -1;  // >= 0: the layout, as in a request's configuration
+  int group_waves = 0;  // 1..8
+};
+DirectShape direct_shape(int dtype, int ranks, uint64_t count, uint64_t span,
+                         const DirectOverride& o);
 
 }  // namespace pcoll
