@@ -315,9 +315,8 @@ __device__ __forceinline__ HostWindow host_window(const ReduceArgs& a,
 // were consumed, the consumed counts are in a word of their own, read again
 // under the lock.)
 //
-// `probe`: a worker that has waited a while looks at one host entry and the
-// ring's word first, so an epoch that waits for its producers keeps no wide
-// bus reads in flight.
+// `probe`: a worker that has waited a while looks at one host entry first, so
+// an epoch that waits for its producers keeps no wide bus reads in flight.
 __device__ __forceinline__ bool try_ingest(const ReduceArgs& a, uint32_t epoch,
                                            uint64_t qs, bool probe,
                                            uint32_t t, uint64_t& qs_out,
@@ -333,15 +332,18 @@ __device__ __forceinline__ bool try_ingest(const ReduceArgs& a, uint32_t epoch,
     hcons = (uint32_t)used;
     dcons = (uint32_t)(used >> 32);
   }
+  bool host = true;
   if (probe) {
+    // both in flight; what the ring holds is taken without waiting for the
+    // host list's round trips over the bus (the next look makes those)
     uint64_t head = 0;
     if (lane == 0 && hcons < a.nparts_total)
       head = ld_rlx_sys64(&a.hlist[hcons]);
-    if ((uint32_t)(uni64(head) >> 32) != epoch &&
-        ring_entries(rw, epoch) <= dcons)
-      return false;
+    host = ring_entries(rw, epoch) <= dcons;
+    if (host && (uint32_t)(uni64(head) >> 32) != epoch) return false;
   }
-  HostWindow h = host_window(a, epoch, hcons);
+  // (past the list's end nothing is read)
+  HostWindow h = host_window(a, epoch, host ? hcons : a.nparts_total);
   const uint32_t dr = ring_entries(rw, epoch);
   if (h.total == 0u && dr <= dcons) return false;
 
@@ -369,7 +371,7 @@ __device__ __forceinline__ bool try_ingest(const ReduceArgs& a, uint32_t epoch,
     dcons = (uint32_t)(used >> 32);
     if ((uint32_t)used != hcons) {  // only duplicates, so qs is the same
       hcons = (uint32_t)used;
-      h = host_window(a, epoch, hcons);
+      h = host_window(a, epoch, host ? hcons : a.nparts_total);
     }
   }
   uint32_t qcount = q_entries(qs), qtiles = q_tiles(qs);
