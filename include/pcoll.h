@@ -366,8 +366,8 @@ typedef struct {
                         epoch gets tiles of about R / (f x workgroups) rows,
                         clamped to [min_tile_elems, tile_elems]; 0 = every
                         tile has tile_elems elements */
-  int unroll;        /* rows (64 lanes x 16 bytes) each lane keeps loading
-                        at once in the int32 / fp32 / bf16 kernels at 3..8
+  int unroll;        /* rows (64 lanes x 16 bytes) of each lane's batch of
+                        loads in the int32 / fp32 / bf16 kernels at 3..8
                         ranks: 4 (the default) or 2, which takes about 40 %
                         fewer registers per wave and leaves room for
                         kernels that run beside the reduction (see
@@ -459,8 +459,8 @@ typedef struct {
   uint64_t kernel_timed;      /* epochs timed (debug non-zero) */
   int groups;                 /* workgroups of the last launch */
   int group_waves;            /* wavefronts per workgroup of the last launch */
-  int unroll;                 /* rows each lane of the last launch keeps
-                                 loading at once: 4 or 2 up to 8 ranks, 2
+  int unroll;                 /* rows of a lane's batch of loads in the last
+                                 launch: 4 or 2 up to 8 ranks, 2
                                  or 1 above (config `unroll` 4 or 2), at
                                  most 2 for bf16 max, 1 in the 8-bit
                                  kernels */

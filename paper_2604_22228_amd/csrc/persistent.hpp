@@ -594,8 +594,8 @@ __device__ __forceinline__ void locate(const ReduceArgs& a, uint32_t t,
 // of one group, and only while the kernel has a backlog of readied work).  A
 // lane for each tile would put 64 atomics of every group on one counter where
 // a partition is large, at 16 ns each: fp32, 8 ranks, 256 MiB each, 1 / 4 / 16
-// partitions 480 / 450 / 436 us that way against 375 now (64 partitions 363
-// either way), 512 MiB in one partition 732 us.
+// partitions, kernel on a cold cache 480 / 450 / 436 us that way against 369 /
+// 367 / 366 now (64 partitions 365 either way), 512 MiB in one partition 732.
 //
 // A group that runs out of work counts itself instead (retire): when the last
 // one has, every tile of the epoch is final, and it stores the epoch into the
@@ -606,8 +606,11 @@ __device__ __forceinline__ void locate(const ReduceArgs& a, uint32_t t,
 // Measured: with ordinary stores, each publication wrote back the XCD's L2
 // (0.2 us alone, and one after the other for the groups of an XCD; 256 groups
 // publishing at the end cost 10 us, so the last tiles were left to the
-// launch's end).  A 4 KiB epoch 18.1 -> 12.4 us of host time, 1 MiB over 4
-// ranks 19.8 -> 15.2 us.
+// launch's end).  With the done word, an epoch of 4 KiB over 8 ranks takes
+// 14.3 us of host time instead of 20.8, of 1 MiB over 4 ranks 16.5 instead of
+// 21.1.  The launch itself ends later by what it now counts: kernel on a cold
+// cache, 8 ranks, 2^10 elements in 4 partitions 8.1 -> 9.0 us, 2^22 32.6 ->
+// 33.9 us, which is what a stream that waits for the epoch sees.
 struct Pending {
   uint32_t part;
   uint32_t nt;

@@ -369,9 +369,8 @@ int resident_groups(int dtype, int op, bool comp, bool deep, int nranks,
   return per_cu > 0 ? per_cu * cus : 0;
 }
 
-// Rows of 64 lanes x 16 bytes each lane of the launch keeps loading at once
-// (the 8-bit kernels: one; the others: the kernels' Unroll rule, at most 2
-// for bf16 max).
+// Rows of 64 lanes x 16 bytes of a lane's batch of loads (the 8-bit kernels:
+// one; the others: the kernels' Unroll rule, at most 2 for bf16 max).
 int rows_in_flight(int dtype, int op, int nranks, bool deep) {
   if (is_fp8(dtype)) return 1;
   int u = nranks <= 2 ? 4 : (nranks <= 8 ? (deep ? 4 : 2) : (deep ? 2 : 1));

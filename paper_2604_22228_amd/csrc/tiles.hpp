@@ -8,9 +8,14 @@
 // partition starts on a 128-byte line of its bucket (partition lengths are
 // planned in whole lines; 256 elements for the 8-bit floats), so a row of a
 // 128-byte aligned buffer covers whole lines.  Each lane streams 16-byte vectors
-// (dwordx4), 64 lanes cover 1 KiB per rank per step, and U steps are issued
-// back to back so that U * P loads are in flight per lane before the first
-// add.  Loads and stores carry the nontemporal hint: the data are touched
+// (dwordx4), 64 lanes cover 1 KiB per rank per step, and U steps form one
+// batch of U * P loads per lane.  Up to 16 loads the compiler mostly issues a
+// batch before its first add; in larger ones it starts the first steps' adds
+// while loads are still to come (most in flight: fp32, 8 ranks, U = 4 12 of
+// 32; int32, 16 ranks, U = 2 10 of 32, U = 1 13 of 16; a single step of 4
+// ranks 2 of 4).  A scheduling barrier that keeps every load first is slower
+// (fp32, 8 ranks, 256 MiB each 375 -> 386 us, int32, 16 ranks, 64 MiB 188 ->
+// 192 us).  Loads and stores carry the nontemporal hint: the data are touched
 // once.  The ragged end (< 16 bytes) of a bucket is done element by element.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -312,11 +317,11 @@ __device__ __forceinline__ void combine_scalar(const char* const (&in)[P],
   }
 }
 
-// Rows each lane loads at once: enough loads in flight, bounded register
-// use.  DEEP (the default) keeps 4 rows in flight up to 8 ranks and 2 above
-// (at 16 ranks 1.4 % faster than 1, with no spills); the shallow form keeps
-// half of that from 3 ranks on, which needs fewer registers and leaves more
-// room for kernels that run beside the reduction.
+// Rows of a lane's batch: enough loads in flight, bounded register use.  DEEP
+// (the default) takes 4 rows up to 8 ranks and 2 above (at 16 ranks 1.4 %
+// faster than 1, with no spills); the shallow form takes half of that from 3
+// ranks on, which needs fewer registers and leaves more room for kernels that
+// run beside the reduction.
 template <int P, bool DEEP>
 struct Unroll {
   static constexpr int value = P <= 2 ? 4 : (P <= 8 ? (DEEP ? 4 : 2) : (DEEP ? 2 : 1));
@@ -424,8 +429,8 @@ struct VecTile {
     constexpr int U0 = Unroll<P, DEEP>::value;
     constexpr bool kBf16Max = Kind == 2 && std::is_same<Acc, FMax>::value;
     constexpr int U = kBf16Max && U0 > 2 ? 2 : U0;
-    // U rows at a time, then U / 2, then one: whatever is left of a tile has
-    // as many loads in flight as it can
+    // U rows at a time, then U / 2, then one: whatever is left of a tile is
+    // loaded in batches as large as it allows
     uint32_t k = wave;
     auto batch = [&](auto depth) {
       constexpr int D = decltype(depth)::value;
