@@ -12,7 +12,7 @@
 namespace pcoll {
 
 template <class Tile, int P>
-__global__ __launch_bounds__(64 * kMaxWavesPerGroup, (Tile::template waves<P>()))
+__global__ __launch_bounds__(64 * kMaxWavesPerGroup, (Tile::template waves<P, false>()))
 void reduce_persistent(
     ReduceArgs a) {
   dev::persistent_loop<Tile, P>(a);
@@ -23,7 +23,7 @@ void reduce_persistent(
 // has room.  No queue, no readiness, no completion beyond the launch's own,
 // so no state besides the arguments.
 template <class Tile, int P>
-__global__ __launch_bounds__(64 * kMaxWavesPerGroup, (Tile::template waves<P>()))
+__global__ __launch_bounds__(64 * kMaxWavesPerGroup, (Tile::template waves<P, true>()))
 void reduce_direct(
     DirectArgs a) {
   const uint32_t wave = dev::uni(threadIdx.x / 64u);

@@ -380,7 +380,7 @@ struct VecTile {
   static constexpr int kElemBytes = Kind >= 2 ? 2 : 4;
   static constexpr int kPerVec = 16 / kElemBytes;
   static constexpr uint32_t kRowElems = 64 * kPerVec;
-  template <int P>
+  template <int P, bool DIRECT>
   static constexpr int waves() { return 2; }
 
   // Reduces wavefront `wave`'s rows of the tile: rows k = wave, wave +
@@ -570,13 +570,15 @@ __device__ __forceinline__ float sum2_at(const uint4 (&raw)[P],
 // span too much for that: such rows take Sum2 at once.
 //
 // Bound: the memory streams, with the arithmetic close behind.  e4m3, 128
-// buckets, 2^30 values, 8 ranks: 1.90 ms with Sum2 for every value, 1.61 ms
+// buckets, 2^30 values, 8 ranks: 1.90 ms with Sum2 for every value, 1.60 ms
 // this way (5.5 TB/s); one message of 2^25 values, 16 ranks, 144 us (binary64
 // sums, which these kernels must not use, 160).  With 3 ranks it costs what
-// Sum2 does (2^26 values, direct kernel 66 / 68 us), with 4 less (76 / 84).
-// Rows that end in Sum2 pay for both: every value equal, 8 ranks, 80 -> 122 us.  The row's sums are kept for
-// the codes, so registers decide the occupancy: a word at a time, the codes
-// through ld_row (141 -> 124 VGPRs, four wavefronts per SIMD).
+// Sum2 does (2^26 values, direct kernel 64 / 68 us), with 4 less (74 / 84).  A
+// ragged last row in the direct kernel, 16 ranks: Sum2 6.8, this way 5.7 us.
+// Rows that end in Sum2 pay for both: every value equal, 8 ranks, 80 -> 122 us.
+// The row's sums are kept for the codes, so registers decide the occupancy: a
+// word at a time, the codes through ld_row (141 -> 120 VGPRs, four wavefronts
+// per SIMD).
 template <class Fmt, int P>
 __device__ __forceinline__ bool row_from_plain(const uint4 (&raw)[P],
                                                const float (&s_in)[P],
@@ -692,11 +694,15 @@ __device__ __forceinline__ uint4 load_codes(const uint8_t* p, uint32_t have) {
 template <bool COMP, class Fmt>
 struct Fp8Tile {
   static constexpr uint32_t kRowElems = 1024;  // 64 lanes x 16 codes
-  // Wavefronts per SIMD that the registers are kept to (more spill): the
-  // loads of others hide behind a row's arithmetic.
-  template <int P>
+  // Wavefronts per SIMD that the registers are kept to, without spills: the
+  // loads of others hide behind a row's arithmetic (8 ranks, 2^26 values,
+  // direct kernel, four instead of five 117 -> 122 us).
+  template <int P, bool DIRECT>
   static constexpr int waves() {
-    return COMP && P >= 3 ? (P <= 8 ? 4 : 3) : 2;
+    if (!COMP || P < 3) return 2;
+    if (DIRECT)
+      return P == 3 ? 7 : (P <= 5 ? 6 : (P <= 8 ? 5 : (P <= 12 ? 4 : 3)));
+    return P <= 9 ? 4 : 3;
   }
 
   // Row q: lane l owns codes el .. el + 16 of block blk.  FULL: the
@@ -730,7 +736,8 @@ struct Fp8Tile {
     uint32_t w[4];
     float so;
     bool done = false;
-    if constexpr (COMP && P >= 3 && FULL)
+    // codes past the end are zeros, which change no sum and no maximum
+    if constexpr (COMP && P >= 3)
       done = row_from_plain<Fmt>(raw, s_in, w, so);
     if (!done) {
       float y[16];
@@ -738,7 +745,7 @@ struct Fp8Tile {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float v[4];
-        sum_word<COMP, COMP && P >= 3 && FULL>(raw, k, dec, v);
+        sum_word<COMP, COMP && P >= 3>(raw, k, dec, v);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           y[4 * k + j] = v[j];
@@ -895,7 +902,7 @@ __device__ __forceinline__ float pair_max(float v) {
 template <bool COMP>
 struct MxTile {
   static constexpr uint32_t kRowElems = 1024;  // 64 lanes x 16 codes
-  template <int P>
+  template <int P, bool DIRECT>
   static constexpr int waves() { return 2; }
 
   template <int P, bool FULL>

@@ -3,8 +3,8 @@ plain binary32 sums (e4m3, e5m2) and integers (MX blocks) wherever that gives
 Sum2's codes and scales.  Finite inputs that leave few or many values open
 (sums halfway between two codes, near ties for a block's largest value, one
 rank far below the others) against the oracle's Sum2; infinities and NaN, in
-codes and scales, against the kernels' own Sum2, which rows that are not
-whole (e4m3, e5m2) or hold a wide spread of scales (MX) take."""
+codes and scales, against the kernels' own Sum2, which a whole row takes when
+it holds an infinite scale (e4m3, e5m2) or scales far apart (MX)."""
 import numpy as np
 import pytest
 import torch
@@ -34,7 +34,8 @@ def _reduce(dtype, q, s, size=None):
     out = torch.full((n,), 0x55, dtype=torch.uint8, device=DEV)
     osc = torch.zeros_like(ds[0])
     cut = [slice(i * size, (i + 1) * size) for i in range(nb)]
-    cuts = [slice(i * size // blk, (i + 1) * size // blk) for i in range(nb)]
+    cuts = [slice(i * size // blk, -(-(i + 1) * size // blk))
+            for i in range(nb)]
     req = new_request([size] * nb, DTYPE[dtype], pc.SUM, 1, q.shape[0], comp=1)
     req.bind([[x[c] for x in dq] for c in cut], [out[c] for c in cut],
              rank_scales=[[x[c] for x in ds] for c in cuts],
@@ -100,6 +101,21 @@ MODES = {"e4m3": ["odd", "equal", "ones", "powers", "spread", "far", "flat",
 MODES["e5m2"] = MODES["e4m3"]
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 255, 257, 700, 1023, 1025])
+@pytest.mark.parametrize("ranks", [2, 3, 8, 16])
+@pytest.mark.parametrize("dtype", ["e4m3", "e5m2"])
+def test_last_row(orc, dtype, ranks, n):
+    say(f"case last row {dtype} P={ranks} n={n}")
+    rng = np.random.default_rng(n)
+    q, s = _inputs(dtype, "odd", ranks, rng)
+    q, s = q[:, :n], s[:, :(n + 255) // 256]
+    gq, gs = _reduce(dtype, q, s)
+    ref = {"e4m3": orc.sum_e4m3_f32, "e5m2": orc.sum_e5m2_f32}[dtype]
+    wq, ws = ref(list(q.copy()), list(s.copy()), comp=True)[:2]
+    assert np.array_equal(as_u32(gs), as_u32(ws))
+    assert np.array_equal(gq, wq)
+
+
 @pytest.mark.parametrize("ranks", [3, 5, 8, 9, 16])
 @pytest.mark.parametrize("dtype,mode",
                          [(d, m) for d in DTYPE for m in MODES[d]])
@@ -143,7 +159,14 @@ def test_special_values_as_sum2(dtype, what, ranks):
     elif what == "nan scale":
         s[1, 5::9] = np.nan
     gq, gs = _reduce(dtype, q, s)
-    wq, ws = _reduce(dtype, q, s, size=256)  # a quarter of a row each
+    # each block beside one of an infinite scale, whose row takes Sum2 itself
+    nb = n // 256
+    q2, s2 = np.zeros((ranks, nb, 512), np.uint8), np.ones((ranks, nb, 2), "f")
+    q2[:, :, :256], s2[:, :, 0] = q.reshape(ranks, nb, 256), s
+    q2[0, :, 256:], s2[0, :, 1] = 0x38, np.inf
+    wq, ws = _reduce(dtype, q2.reshape(ranks, -1), s2.reshape(ranks, -1),
+                     size=512)
+    wq, ws = wq.reshape(nb, 512)[:, :256].reshape(-1), ws.reshape(nb, 2)[:, 0]
     assert np.array_equal(as_u32(gs), as_u32(ws))
     assert np.array_equal(gq, wq)
 
