@@ -70,6 +70,10 @@ INTERLEAVE_8BIT = (0, 1, 4, 8, 16)
 # on the largest key's row also covers all larger sizes, else twice its size.
 # Other sizes, ranks and types take the library's rule (tuning.cpp)
 REACH_DOWN, ALL_FROM = 2, 24
+# Shapes this close to a key's fastest are the same within the noise of a run
+# (0.1 to 0.3 % between runs): the first of them in grid order is taken, the
+# one of smaller tiles, fewer workgroups and fewer registers
+SAME = 1.003
 
 
 def grid_for(dtype, ranks=8):
@@ -190,7 +194,7 @@ def tune(keys, grid, warmup, reps, log=print):
         bufs = make_buffers(pc, torch, synth, dtype, ranks, counts)
         nbytes = sum(counts) * pc.ELEM_BYTES[dtype]
         lg = int(math.floor(math.log2(max(nbytes, 1))))
-        best = None
+        timed = []
         parts_list = nparts if isinstance(nparts, tuple) else (nparts,)
         for choice in itertools.product(*(grid or grid_for(dtype, ranks))):
             ms = statistics.mean(
@@ -204,8 +208,9 @@ def tune(keys, grid, warmup, reps, log=print):
                             "interleave": choice[2], "waves": choice[3],
                             "batch": choice[4], "unroll": choice[5],
                             "ms": round(ms, 5)}))
-            if best is None or ms < best[0]:
-                best = (ms, choice)
+            timed.append((ms, choice))
+        fastest = min(timed)[0]
+        best = next(t for t in timed if t[0] <= SAME * fastest)
         # a direct launch's row also serves graph replays of keys tuned
         # for direct launches only
         rows.append((DTYPE_NAMES[dtype], OP_NAMES[op], ranks,

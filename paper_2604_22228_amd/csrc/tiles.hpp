@@ -569,16 +569,16 @@ __device__ __forceinline__ float sum2_at(const uint4 (&raw)[P],
 // two codes; below 2^24 such multiples they are exact (E = 0).  e5m2 codes
 // span too much for that: such rows take Sum2 at once.
 //
-// Bound: the memory streams, with the arithmetic close behind.  e4m3, 128
-// buckets, 2^30 values, 8 ranks: 1.90 ms with Sum2 for every value, 1.60 ms
-// this way (5.5 TB/s); one message of 2^25 values, 16 ranks, 144 us (binary64
-// sums, which these kernels must not use, 160).  With 3 ranks it costs what
-// Sum2 does (2^26 values, direct kernel 64 / 68 us), with 4 less (74 / 84).  A
-// ragged last row in the direct kernel, 16 ranks: Sum2 6.8, this way 5.7 us.
-// Rows that end in Sum2 pay for both: every value equal, 8 ranks, 80 -> 122 us.
-// The row's sums are kept for the codes, so registers decide the occupancy: a
-// word at a time, the codes through ld_row (141 -> 120 VGPRs, four wavefronts
-// per SIMD).
+// Bound: VALU issue (686 instructions a row at 8 ranks, 0.78 per CU and cycle)
+// beside the memory streams.  e4m3, 128 buckets, 2^30 values, 8 ranks: 1.90 ms
+// with Sum2 for every value, 1.60 ms this way (5.5 TB/s); one message of 2^25
+// values, 16 ranks, 144 us (binary64 sums, which these kernels must not use,
+// 160).  With 3 ranks it costs what Sum2 does (2^26 values, direct kernel 64 /
+// 68 us), with 4 less (74 / 84).  A ragged last row in the direct kernel, 16
+// ranks: Sum2 6.8, this way 5.7 us.  Rows that end in Sum2 pay for both: every
+// value equal, 8 ranks, 80 -> 122 us.  The row's sums are kept for the codes, so
+// registers decide the occupancy: a word at a time, the codes through ld_row
+// (141 -> 120 VGPRs, four wavefronts per SIMD).
 template <class Fmt, int P>
 __device__ __forceinline__ bool row_from_plain(const uint4 (&raw)[P],
                                                const float (&s_in)[P],
